@@ -13,7 +13,8 @@
 //     a step are relaxed together, one lane per edge, in windows of 64
 //     edges: a prefix sum of the settled nodes' degrees places their edge
 //     segments, a prefix maximum over marked segment starts tells every lane
-//     whose edge it holds.  Every CSR record carries the neighbour's CSR
+//     whose edge it holds, and one 16-byte read of the node table's bucket
+//     finds the entry of a neighbour that was visited before.  Every CSR record carries the neighbour's CSR
 //     range and lightest edge, so one round of global loads per window is
 //     all a step needs.  Float sums are monotone, so the distances equal
 //     those of a sequential Dijkstra in the same precision, and a settled
@@ -52,34 +53,81 @@ namespace epic {
 
 namespace {
 
-// Home slot of node v in a table of hcap slots (multiplicative hash, then
-// the product range reduction, so hcap need not be a power of two).
-__device__ __forceinline__ u32 node_slot(int v, u32 hcap) {
-    return (u32)(((u64)((u32)v * 2654435761u) * hcap) >> 32);
-}
-
 // Compiler-only ordering of the wavefront's LDS accesses (see above).
 __device__ __forceinline__ void lds_order() { __asm__ __volatile__("" ::: "memory"); }
 
-// Node table slot: the node in the high bits over its entry (EB bits; the
-// all-ones entry marks a node that got no entry), all ones when empty.
-// 256-entry tables pack both into 32 bits (nodes below 2^23 - 1), larger
-// ones into 64.
+// Node table: an open-addressing hash of the visited nodes.  A slot holds
+// the node in the high bits over its entry (EB bits; the all-ones entry
+// marks a node that got no entry), all ones when empty.  256-entry tables
+// pack both into 32 bits (nodes below 2^23 - 1), larger ones into 64.  The
+// slots are read in buckets of 16 bytes (one LDS read): a node sits at the
+// first slot that was empty, in slot order, from the start of its home
+// bucket on, and slots are never freed, so a bucket with an empty slot ends
+// every search that reaches it.  Five of six edges lead to a node that is
+// in the table already, and a bucket is seldom full, so most edges find
+// their entry with that one read; probing slot by slot with a
+// compare-and-swap each cost the wavefront as many round trips as its
+// unluckiest lane needed.  With the lane state kept as numbers and the
+// window's atomics left to lanes that hold an edge (together 2960 -> 2750
+// vector, 1820 -> 1510 scalar instructions a match): 64 mixed pairs, 473
+// thousand matches, K = 100: 2.07 -> 1.84 ms; 2048 x 1080 with 40000: 199 ->
+// 174 us; 1024 x 436 with 8000: 55.7 -> 48.7 us (kernel trace).
 template <int VCAP>
 struct NodeSlot {
     using T = typename std::conditional<(VCAP <= 256), u32, u64>::type;
+    static constexpr int SLOTS = VCAP + VCAP / 2;            // load at most 2/3
+    static constexpr int BW = 16 / (int)sizeof(T);           // slots per bucket
+    static constexpr int NB = SLOTS / BW;
     static constexpr int EB = VCAP <= 256 ? 9 : 32;
     static constexpr T EMPTY = ~(T)0;
     static constexpr u32 NO_ENTRY = VCAP <= 256 ? 0x1ffu : 0xffffffffu;
     static_assert(VCAP <= 256 ? VCAP < 0x1ff : true, "entry field");
+    static_assert(SLOTS % BW == 0 && SLOTS >= VCAP + 64, "every window's nodes find an empty slot");
     __device__ static T pack(int v, u32 e) { return ((T)(u32)v << EB) | (T)e; }
     __device__ static int node(T w) { return (int)(w >> EB); }
     __device__ static u32 entry(T w) { return (u32)(w & (T)NO_ENTRY); }
+    // First slot of node v's home bucket: a multiplicative hash, then the
+    // product range reduction (NB need not be a power of two).  Nodes of
+    // 32-bit slots take the 24-bit multiplies, which run at the full rate
+    // (the compiler would make the first one a 32-bit multiply): the low 24
+    // bits of v times the golden ratio are a fraction, its product with NB
+    // the bucket.
+    __device__ static u32 home(int v) {
+        if constexpr (sizeof(T) == 4) {
+            u32 h, b;
+            __asm__("v_mul_u32_u24 %0, %1, %2" : "=v"(h) : "s"(0x9e3779u), "v"(v));
+            __asm__("v_mul_hi_u32_u24 %0, %1, %2" : "=v"(b) : "s"((u32)SLOTS << 8), "v"(h));
+            return b & ~(u32)(BW - 1);
+        } else {
+            return (u32)(((u64)((u32)v * 2654435761u) * (u32)NB) >> 32) * BW;
+        }
+    }
+    // Looks for node v in its home bucket, at slot b: its entry, or a number
+    // of VCAP or more when it is not there; `slot` is then the first slot to
+    // try (the bucket's first empty one, or the next bucket's when full).
+    __device__ static u32 find(const T* htab, u32 b, int v, u32& slot) {
+        if constexpr (sizeof(T) == 4) {
+            const uint4 w = *reinterpret_cast<const uint4*>(htab + b);
+            const u32 t = (u32)v << EB;
+            slot = b + (w.x != EMPTY) + (w.y != EMPTY) + (w.z != EMPTY) + (w.w != EMPTY);
+            // a slot of v leaves its entry, any other slot more
+            return min(min(w.x ^ t, w.y ^ t), min(w.z ^ t, w.w ^ t));
+        } else {
+            const ulonglong2 w = *reinterpret_cast<const ulonglong2*>(htab + b);
+            slot = b + (w.x != EMPTY) + (w.y != EMPTY);
+            return w.x != EMPTY && node(w.x) == v ? entry(w.x) : w.y != EMPTY && node(w.y) == v ? entry(w.y) : ~0u;
+        }
+    }
+    // Whether a slot read as w is taken by another node than v.
+    __device__ static bool other(T w, int v) {
+        if constexpr (sizeof(T) == 4) return min(w ^ ((u32)v << EB), ~w) > NO_ENTRY;     // (one compare)
+        else return w != EMPTY && node(w) != v;
+    }
 };
 
 template <int VCAP, bool F64>
 struct KnnLds {
-    static constexpr int HCAP = VCAP + VCAP / 2;   // node table slots (load at most 2/3)
+    static constexpr int HCAP = NodeSlot<VCAP>::SLOTS;
     static constexpr int TW = 64;                 // edges per relaxation window (one per lane)
     using DT = typename std::conditional<F64, u64, u32>::type;     // distance bits
     using RT = typename std::conditional<F64, double, float>::type;
@@ -87,13 +135,15 @@ struct KnnLds {
     // entry e: tentative distance (2e) and lightest incident edge (2e + 1);
     // FP32 packs the edge's high 16 float bits over the degree (low 16 bits),
     // the CSR record's own word.  After the search: the sort keys.
-    alignas(16) DT dm[2 * VCAP];
-    // entry e: CSR start (FP64: and degree); after the search, the entry's node
-    u32 rd[F64 ? 2 * VCAP : VCAP];
-    ST htab[HCAP];                // node table
+    alignas(16) DT dm[2 * VCAP + 2];                // (the last entry takes what does not fit)
+    // entry e: CSR start (FP64: and degree), once settled less its offset in
+    // the step's edges; after the search, the entry's node
+    alignas(16) u32 rd[F64 ? 2 * VCAP + 4 : VCAP + 4];
+    alignas(16) ST htab[HCAP];    // node table
+    alignas(16) u32 head[TW + 4]; // ((1 + position) << 12) | (1 + entry) of the edge segment
+                                  // starting at a window position, 0 elsewhere (and one that
+                                  // takes the marks beyond the window)
     int snode[F64 ? VCAP : 1];    // FP64: node of each sort key
-    u32 head[TW];                 // (window stamp << 12) | (1 + entry) of the edge segment
-                                  // starting at a window position
 };
 
 template <bool F64>
@@ -105,22 +155,6 @@ template <bool F64>
 __device__ __forceinline__ typename std::conditional<F64, u64, u32>::type to_bits(
     typename std::conditional<F64, double, float>::type v) {
     if constexpr (F64) return bitsd(v); else return __float_as_uint(v);
-}
-
-// Distance and lightest edge of entry e (one LDS read).
-template <int VCAP, bool F64>
-__device__ __forceinline__ void read_dm(const KnnLds<VCAP, F64>& S, int e,
-                                        typename KnnLds<VCAP, F64>::RT& d,
-                                        typename KnnLds<VCAP, F64>::RT& mi) {
-    if constexpr (F64) {
-        const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(&S.dm[2 * e]);
-        d = dbits(v.x);
-        mi = dbits(v.y);
-    } else {
-        const uint2 v = *reinterpret_cast<const uint2*>(&S.dm[2 * e]);
-        d = __uint_as_float(v.x);
-        mi = __uint_as_float(v.y);
-    }
 }
 
 // Value of v in lane (this lane xor j); j is a power of two below 64 that
@@ -179,11 +213,11 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
     const RT RINF = (RT)INFINITY;
     constexpr int HCAP = LdsT::HCAP;
     constexpr int TW = LdsT::TW;
-    constexpr int Q = TW / 64;          // edges per lane per window
+    static_assert(TW == 64, "an edge per lane");
     constexpr int R = VCAP / 64;        // entries per lane
     using NS = NodeSlot<VCAP>;
     using ST = typename NS::T;
-    static_assert(VCAP < 4096 && TW <= 128, "head mark layout");
+    static_assert(VCAP < 4096, "head mark layout");
     constexpr int RK = KMAX / 64;
     const int lane = threadIdx.x;
     const int K = P.K;
@@ -196,12 +230,21 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
     // read once: the LDS ordering points below would make the compiler
     // reload it from the descriptor at every window
     const uint4* const adj = P.adj;
+    const u32 last_rec = (u32)P.hash_cap - 1u;
 
     // ------------------------------------------------------------ Dijkstra
-    for (int i = lane; i < HCAP; i += 64) htab[i] = NS::EMPTY;
-    for (int i = lane; i < TW; i += 64) S.head[i] = 0u;
-    for (int i = lane; i < 2 * VCAP; i += 64) S.dm[i] = to_bits<F64>(RINF);
-    for (int i = lane; i < (F64 ? 2 * VCAP : VCAP); i += 64) S.rd[i] = 0u;
+    // entries not in use read as distance infinity, lightest edge and degree
+    // 0: never the frontier minimum, never settled
+    {
+        const uint4 ones = make_uint4(~0u, ~0u, ~0u, ~0u), zero = make_uint4(0u, 0u, 0u, 0u);
+        uint4* const t = reinterpret_cast<uint4*>(htab);
+        for (int i = lane; i < NS::NB; i += 64) t[i] = ones;
+        if (lane < TW / 4) reinterpret_cast<uint4*>(S.head)[lane] = zero;
+        uint4* const dmq = reinterpret_cast<uint4*>(S.dm);
+        const uint4 unused = F64 ? make_uint4(0u, (u32)(DOUBLE_INF_BITS >> 32), 0u, 0u)
+                                 : make_uint4(FLOAT_INF_BITS, 0u, FLOAT_INF_BITS, 0u);
+        for (int i = lane; i < 2 * VCAP * (int)sizeof(typename LdsT::DT) / 16; i += 64) dmq[i] = unused;
+    }
     __syncthreads();
     if (lane == 0) {
         const u32 a = gmem(P.row_ptr)[s], b = gmem(P.row_ptr)[s + 1];
@@ -215,249 +258,196 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
             S.dm[1] = (gmem(P.minin)[s] & 0xffff0000u) | (b - a);
             S.rd[0] = a;
         }
-        htab[node_slot(s, HCAP)] = NS::pack(s, 0u);
+        htab[NS::home(s)] = NS::pack(s, 0u);
     }
     __syncthreads();
 
     int nvis = 1;               // entries in use (the same in every lane)
-    int stamp = 0;              // relaxation windows so far (head marks)
     int nsettled = 0;           // settled entries (the same in every lane)
-    bool ovf = false;
-    // per group r: the lanes whose entry lane + 64 r is settled, as a lane
-    // mask (uniform: the per-lane tests are mask selects, updates scalar)
-    u64 smask[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) smask[r] = 0ull;
-    // per group r: the raw (distance, lightest edge) bits and CSR range of
-    // entry lane + 64 r, kept across steps as loaded
+    // Lane state of group r, entry lane + 64 r: its distance as last read,
+    // infinity once it is settled (0 before), its edges in this step (0
+    // unless settled in it) and where they start among the step's edges.
+    // Kept as numbers, not as lane masks: the scalar unit, shared by the
+    // CU's four SIMDs, is nearly as busy with this kernel as the SIMDs are.
     using DT2 = typename std::conditional<F64, ulonglong2, uint2>::type;
-    DT2 dmr[R];
-    u32 deg[R];
-    RT d[R], mi[R];
+    RT d[R], sf[R];
+    u32 dg[R], off[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        dmr[r].x = dmr[r].y = to_bits<F64>(RINF);
-        deg[r] = 0u;
+        d[r] = RINF;
+        sf[r] = (RT)0;
+        dg[r] = off[r] = 0u;
     }
     RT dstop = RINF;
-    for (;;) {
-        // nvis and nsettled are the same in every lane; readfirstlane lets
-        // the compiler keep them (and the branches on them) scalar
-        const int nv = __builtin_amdgcn_readfirstlane(nvis);
-        nsettled = __builtin_amdgcn_readfirstlane(nsettled);
-        // only the groups of 64 entries that are in use are read and
-        // scanned (a uniform bound); d[r] of the others stays infinite
-        const int ru = (nv + 63) >> 6;
-        // entries not in use read as (inf, inf, 0, 0): the table is filled
-        // with them at the start, so the reads need no predicate; groups
-        // beyond ru keep those values from before the loop
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (r < ru) {
-                const int e = lane + 64 * r;
-                dmr[r] = *reinterpret_cast<const DT2*>(&S.dm[2 * e]);
-                if constexpr (F64) deg[r] = S.rd[2 * e + 1];
-            }
-            d[r] = from_bits<F64>(dmr[r].x);
-            if constexpr (F64) {
-                mi[r] = from_bits<F64>(dmr[r].y);
-            } else {
-                mi[r] = __uint_as_float(dmr[r].y & 0xffff0000u);
-                deg[r] = dmr[r].y & 0xffffu;
-            }
-        }
-        // frontier minimum (entries not in use are infinite)
+    // One step on the groups in use (RU of them, or with RU = 0 `ru`, known
+    // at run time; on the 64-pair batch 1 % faster with RU than with a branch
+    // per group): settles the final frontier nodes and marks where their
+    // edges start in the step's first window.  Returns the number of edges,
+    // or -1 when the search is done.
+    auto step = [&](auto ru_c, int ru) -> int {
+        constexpr int RU = decltype(ru_c)::value;
+        RT mi[R], x[R];          // x: the distance on the frontier, infinite elsewhere
         RT fmin = RINF;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const RT dv = __builtin_amdgcn_inverse_ballot_w64(smask[r]) ? RINF : d[r];
-            if constexpr (F64) fmin = fmin < dv ? fmin : dv;
-            else fmin = __uint_as_float(min(__float_as_uint(fmin), __float_as_uint(dv)));   // d >= 0
+            if (RU ? r >= RU : r >= ru) continue;
+            const DT2 v = *reinterpret_cast<const DT2*>(&S.dm[2 * (lane + 64 * r)]);
+            d[r] = from_bits<F64>(v.x);
+            if constexpr (F64) {
+                mi[r] = dbits(v.y);
+                dg[r] = S.rd[2 * (lane + 64 * r) + 1];
+                x[r] = sf[r] > d[r] ? sf[r] : d[r];
+                fmin = fmin < x[r] ? fmin : x[r];
+            } else {
+                mi[r] = __uint_as_float(v.y & 0xffff0000u);
+                dg[r] = v.y & 0xffffu;
+                x[r] = __uint_as_float(max(__float_as_uint(d[r]), __float_as_uint(sf[r])));
+                fmin = __uint_as_float(min(__float_as_uint(fmin), __float_as_uint(x[r])));
+            }
         }
         RT dmin;
         if constexpr (F64) dmin = wave::min(fmin); else dmin = wave::min_nonneg(fmin);
-        // settled entries strictly below the frontier minimum (only counted
-        // once enough entries are settled at all)
+        // entries strictly below the frontier minimum are settled (only
+        // counted once enough entries are settled at all)
         int below = 0;
         if (nsettled >= keff) {
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                if (r < ru) below += __popcll(wave::ballot(d[r] < dmin) & smask[r]);
+                if (RU ? r < RU : r < ru) below += __popcll(wave::ballot(d[r] < dmin));
         }
         if (below >= keff || !(dmin < RINF)) {
             dstop = dmin;       // nodes settled at this point lie at or above dmin
-            break;
+            return -1;
         }
         // settle the final frontier nodes; their edges are relaxed below
-        u64 newly[R];
-        int my_edges = 0;
+        u32 my_edges = 0u;
+        bool newly[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            newly[r] = 0ull;
-            if (r >= ru) continue;
-            const int nin = nv - 64 * r;                       // entries of group r in use, >= 1
-            const u64 valid = nin >= 64 ? ~0ull : (1ull << nin) - 1ull;
-            newly[r] = wave::ballot(d[r] <= dmin + mi[r]) & valid & ~smask[r];
-            nsettled += __popcll(newly[r]);
-            smask[r] |= newly[r];
-            if (__builtin_amdgcn_inverse_ballot_w64(newly[r])) my_edges += (int)deg[r];
+            newly[r] = false;
+            if (RU ? r >= RU : r >= ru) continue;
+            const u64 m = wave::ballot(x[r] <= dmin + mi[r]);
+            newly[r] = __builtin_amdgcn_inverse_ballot_w64(m);
+            nsettled += __popcll(m);
+            sf[r] = newly[r] ? RINF : sf[r];
+            dg[r] = newly[r] ? dg[r] : 0u;
+            my_edges += dg[r];
         }
-        const int incl = wave::incl_scan(my_edges);
-        const int T = __builtin_amdgcn_readlane(incl, 63);
-        int off[R];
-        {
-            int o = incl - my_edges;
+        const u32 incl = (u32)wave::incl_scan((int)my_edges);
+        // a settled node's CSR start less the start of its edges in this
+        // step turns an edge's position into its record's index; positions
+        // beyond the first window are marked when their window comes
+        u32 o = incl - my_edges;
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                off[r] = o;
-                if (r < ru && __builtin_amdgcn_inverse_ballot_w64(newly[r])) o += (int)deg[r];
+        for (int r = 0; r < R; ++r) {
+            if (RU ? r >= RU : r >= ru) continue;
+            off[r] = o;
+            if (newly[r]) {
+                const u32 at = min(o, (u32)TW);
+                S.head[at] = (at << 12) + (u32)((1 << 12) + lane + 64 * r + 1);
+                atomicSub(&S.rd[(F64 ? 2 : 1) * (lane + 64 * r)], o);
             }
+            o += dg[r];
         }
-        int carry_start = 0, carry_e = 0;
-        for (int wb = 0; wb < T; wb += TW) {
-            // mark the segments that start in this window; marks carry the
-            // window's stamp, so stale ones from earlier windows are ignored
-            // and the array is never cleared (except when the stamp wraps)
-            if (++stamp == (1 << 20)) {
-                for (int i = lane; i < TW; i += 64) S.head[i] = 0u;
-                lds_order();
-                stamp = 1;
-            }
-            const u32 stamp_hi = (u32)stamp << 12;
+        return __builtin_amdgcn_readlane((int)incl, 63);
+    };
+    for (;;) {
+        // nvis and nsettled are the same in every lane; readfirstlane lets
+        // the compiler keep them (and the branches on them) scalar
+        nvis = __builtin_amdgcn_readfirstlane(nvis);
+        nsettled = __builtin_amdgcn_readfirstlane(nsettled);
+        const int ru = (nvis + 63) >> 6;
+        int T;
+        if constexpr (R <= 4) {
+            // the groups in use known at compile time: no branch per group
+            T = ru == 1 ? step(std::integral_constant<int, 1>{}, ru) : ru == 2 ? step(std::integral_constant<int, 2>{}, ru)
+              : ru == 3 ? step(std::integral_constant<int, 3>{}, ru) : step(std::integral_constant<int, R>{}, ru);
+        } else {
+            T = step(std::integral_constant<int, 0>{}, ru);
+        }
+        if (T < 0) break;
+        u32 carry = 0u;             // 1 + entry of the segment that reaches into the next window
+        for (int wb = 0; wb < T && nvis <= VCAP; wb += TW) {
+            if (wb > 0) {
+                // mark the segments that start in this window (a node reached
+                // by an edge has at least that edge, so no two start at one place)
 #pragma unroll
-            for (int r = 0; r < R; ++r)
-                if (r < ru && __builtin_amdgcn_inverse_ballot_w64(newly[r]) && deg[r] > 0u && off[r] >= wb &&
-                    off[r] < wb + TW)
-                    S.head[off[r] - wb] = stamp_hi | (u32)(lane + 64 * r + 1);
-            lds_order();
-            const int nq = min(Q, (T - wb + 63) >> 6);   // chunks of 64 edges in this window
-            bool act[Q];
-            int qe[Q], qst[Q];
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                act[q] = false;
-                qe[q] = 0;
-                qst[q] = 0;
-                if (q < nq) {
-                    act[q] = wb + 64 * q + lane < T;
-                    const u32 hv = S.head[64 * q + lane];
-                    // (window position, entry) of the last segment start at
-                    // or before this lane, plus one (0: none in this chunk)
-                    const u32 sc = wave::incl_max((hv >> 12) == (u32)stamp
-                                                      ? ((u32)(64 * q + lane) << 12) | (hv & 0xfffu) : 0u);
-                    if (sc != 0u) {
-                        qst[q] = wb + (int)(sc >> 12);
-                        qe[q] = (int)(sc & 0xfffu) - 1;
-                    } else {
-                        qst[q] = carry_start;
-                        qe[q] = carry_e;
-                    }
-                    carry_start = __builtin_amdgcn_readlane(qst[q], 63);
-                    carry_e = __builtin_amdgcn_readlane(qe[q], 63);
+                for (int r = 0; r < R; ++r) {
+                    const u32 at = off[r] - (u32)wb;
+                    if (r < ru && dg[r] != 0u && at < (u32)TW)
+                        S.head[at] = (at << 12) + (u32)((1 << 12) + lane + 64 * r + 1);
                 }
             }
-            // each lane's edges: source entry's CSR start and settled distance
-            RT du[Q];
-            u32 ei[Q];
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                RT unused;
-                read_dm<VCAP, F64>(S, qe[q], du[q], unused);
-                const u32 st = S.rd[F64 ? 2 * qe[q] : qe[q]];
-                ei[q] = act[q] ? st + (u32)(wb + 64 * q + lane - qst[q]) : 0u;
+            lds_order();
+            // the last segment start at or before this lane; the marks are
+            // taken back as they are read
+            const u32 hv = atomicExch(&S.head[lane], 0u);
+            const u32 seg = wave::incl_max(max(hv, carry)) & 0xfffu;
+            carry = (u32)__builtin_amdgcn_readlane((int)seg, 63);
+            // this lane's edge: its source's settled distance and its record
+            // (lanes beyond the last edge read some record of the array and
+            // look for the source s, which is in the table)
+            const bool act = lane < T - wb;
+            const u32 qe = seg - 1u;
+            const RT du = from_bits<F64>(S.dm[2 * qe]);
+            const u32 ei = min(S.rd[F64 ? 2 * qe : qe] + (u32)wb + (u32)lane, last_rec);
+            // (32-bit slots: nodes below 2^23, so the records lie within 2 GiB)
+            const uint4 rec = sizeof(ST) == 4
+                                  ? gload(reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(adj) + (ei << 4)))
+                                  : gload(adj + ei);
+            RT cand;
+            u64 nbm = 0ull;
+            if constexpr (F64) {
+                cand = du + gmem(P.adjw64)[ei];
+                nbm = gmem(P.nbmin64)[ei];
+            } else {
+                cand = du + __uint_as_float(rec.y);
             }
-            uint4 rec[Q];
-            RT cand[Q], nbm[Q];
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                rec[q] = gload(adj + ei[q]);
+            const int v = act ? (int)rec.x : s;
+            // find the neighbour's entry in the node table, or claim the
+            // first empty slot, which several lanes of this window may try
+            // for (the swap returns the slot's node when it is taken; the
+            // table always has an empty slot)
+            u32 slot;
+            u32 e = NS::find(htab, NS::home(v), v, slot);
+            ST prev = 0;
+            if (e >= (u32)VCAP) {
+                for (;;) {
+                    if (slot == (u32)HCAP) slot = 0u;
+                    prev = atomicCAS(&htab[slot], NS::EMPTY, NS::pack(v, NS::NO_ENTRY));
+                    if (!NS::other(prev, v)) break;
+                    ++slot;
+                }
+            }
+            // the nodes claimed here get entries (their distance, lightest
+            // edge and CSR range)
+            const u64 m = wave::ballot(prev == NS::EMPTY);
+            if (__builtin_amdgcn_inverse_ballot_w64(m)) {
+                const u32 en = min((u32)(nvis + wave::lanes_below(m)), (u32)VCAP);
+                S.dm[2 * en] = to_bits<F64>(cand);
                 if constexpr (F64) {
-                    cand[q] = du[q] + gmem(P.adjw64)[ei[q]];
-                    nbm[q] = dbits(gmem(P.nbmin64)[ei[q]]);
+                    S.dm[2 * en + 1] = nbm;
+                    S.rd[2 * en] = rec.z;
+                    S.rd[2 * en + 1] = rec.w;
                 } else {
-                    // the record carries the neighbour's lightest edge rounded
-                    // down to 16 bits: a lower bound, which is all the settle
-                    // test needs
-                    cand[q] = du[q] + __uint_as_float(rec[q].y);
-                    nbm[q] = __uint_as_float(rec[q].w & 0xffff0000u);
+                    // lightest edge bits over the degree; the edge was
+                    // rounded down to 16 bits: a lower bound, which is all
+                    // the settle test needs
+                    S.dm[2 * en + 1] = rec.w;
+                    S.rd[en] = rec.z;
                 }
+                htab[slot] = NS::pack(v, en);
             }
-            // find or claim each neighbour's table slot with one
-            // compare-and-swap per probe: it returns an empty slot (this
-            // lane claimed it, for now without an entry), a slot of v
-            // (already there) or of another node (next slot).
-            // res: 0 while probing, else 1 + slot, bit 30 set when this lane
-            // claimed it; RES_IDLE for lanes without an edge.
-            constexpr u32 RES_WON = 1u << 30, RES_IDLE = ~0u;
-            u32 res[Q], hh[Q];
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                res[q] = act[q] ? 0u : RES_IDLE;
-                hh[q] = node_slot((int)rec[q].x, HCAP);
-            }
-            for (int probe = 0; probe < HCAP; ++probe) {
-                bool any = false;
-#pragma unroll
-                for (int q = 0; q < Q; ++q) any = any || res[q] == 0u;
-                if (wave::ballot(any) == 0ull) break;
-                ST prev[Q];             // all chunks' compare-and-swaps in flight together
-#pragma unroll
-                for (int q = 0; q < Q; ++q)
-                    prev[q] = res[q] == 0u ? atomicCAS(&htab[hh[q]], NS::EMPTY, NS::pack((int)rec[q].x, NS::NO_ENTRY))
-                                           : (ST)0;
-#pragma unroll
-                for (int q = 0; q < Q; ++q) {
-                    if (res[q] == 0u) {
-                        res[q] = prev[q] == NS::EMPTY ? (hh[q] + 1u) | RES_WON
-                               : NS::node(prev[q]) == (int)rec[q].x ? hh[q] + 1u : 0u;
-                        hh[q] = hh[q] + 1u == (u32)HCAP ? 0u : hh[q] + 1u;
-                    }
-                }
-            }
-            {
-                bool lost = false;
-#pragma unroll
-                for (int q = 0; q < Q; ++q) lost = lost || res[q] == 0u;
-                if (wave::ballot(lost) != 0ull) ovf = true;
-            }
-            // new nodes get entries (with their distance and CSR range)
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const bool won = res[q] != RES_IDLE && (res[q] & RES_WON) != 0u;
-                const u64 m = wave::ballot(won);
-                const int e = nvis + wave::lanes_below(m);
-                nvis += __popcll(m);
-                if (won) {
-                    const u32 hs = (res[q] & (RES_WON - 1u)) - 1u;
-                    if (e < VCAP) {
-                        S.dm[2 * e] = to_bits<F64>(cand[q]);
-                        if constexpr (F64) {
-                            S.dm[2 * e + 1] = to_bits<F64>(nbm[q]);
-                            S.rd[2 * e] = rec[q].z;
-                            S.rd[2 * e + 1] = rec[q].w;
-                        } else {
-                            S.dm[2 * e + 1] = rec[q].w;        // lightest edge bits over the degree
-                            S.rd[e] = rec[q].z;
-                        }
-                        htab[hs] = NS::pack((int)rec[q].x, (u32)e);
-                    }
-                }
-            }
-            if (nvis > VCAP) ovf = true;
+            nvis += __popcll(m);
             lds_order();
-            // relax the nodes that were already in the table
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                if (res[q] != RES_IDLE && res[q] != 0u && (res[q] & RES_WON) == 0u) {
-                    const u32 e = NS::entry(htab[res[q] - 1u]);
-                    if (e != NS::NO_ENTRY) atomicMin(&S.dm[2 * e], to_bits<F64>(cand[q]));
-                }
-            }
+            // relax: nodes claimed in this window have their entries by now
+            if (e >= (u32)VCAP) e = NS::entry(htab[slot]);
+            // (lanes without an edge stay out: atomics on one address go one by one)
+            if (act) atomicMin(&S.dm[2 * e], to_bits<F64>(cand));
             lds_order();
         }
-        if (ovf) break;
+        if (nvis > VCAP) return false;
     }
-    if (ovf) return false;
 
     // ---------------------------------------- select the K nearest (sorted)
     // Candidates: settled entries strictly below dstop, sorted in LDS: FP32
@@ -470,13 +460,13 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
     for (int h = lane; h < HCAP; h += 64) {
         const ST w = htab[h];
         const u32 e = NS::entry(w);
-        if (w != NS::EMPTY && e < (u32)VCAP) node_of[e] = NS::node(w);
+        if (e < (u32)VCAP) node_of[e] = NS::node(w);         // (an empty slot's entry field is no entry)
     }
     __syncthreads();                 // the distances (the keys' space) are in registers from here
     int nc = 0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const bool c = __builtin_amdgcn_inverse_ballot_w64(smask[r]) && d[r] < dstop;
+        const bool c = d[r] < dstop;         // settled: nothing on the frontier lies below dstop
         const u64 m = wave::ballot(c);
         const int pos = nc + wave::lanes_below(m);
         nc += __popcll(m);
@@ -643,11 +633,10 @@ __device__ __forceinline__ bool knn_active(const PairDev& P, int s) {
 }  // namespace
 
 // First launch: one block (one wavefront) per match of every pair.
-// At most 80 scalar registers: with the 82 the compiler otherwise takes,
-// the hardware's allocation granule leaves room for 7 wavefronts per SIMD,
-// not 8 (the dispatcher's SGPR-full stall counter says so, with LDS, VGPRs
-// and wave slots all free), and the last 832 of 8000 matches start only as
-// the first ones end; at 78 all of them start at once.
+// At most 80 scalar registers: beyond that the hardware's allocation granule
+// leaves room for 7 wavefronts per SIMD, not 8 (an earlier form of the search
+// took 82, and the dispatcher's SGPR-full stall counter showed the last 832
+// of 8000 matches waiting for the first ones to end).
 template <int VCAP, int KMAX, bool F64>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_num_sgpr(80))) void k_knn_fit(
     const PairDev* __restrict__ pairs, RunDev run) {
