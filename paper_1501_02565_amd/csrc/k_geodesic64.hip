@@ -295,7 +295,7 @@ __global__ __launch_bounds__(256) void k_geo64_pass(const PairDev* __restrict__ 
     if (threadIdx.x == 0) dirty[tile] = 0u;
     const int border = visit64<CONN, PHASE>(P, tx, ty, S, P.counters + C_GEOERR, kPass64Rounds);
     if (threadIdx.x == 0) {
-        atomicAdd(&P.counters[C_TILE_VISITS], 1);
+        count_visits(P, tile, 1);
         if (border) {
             mark64<CONN>(P, run, tx, ty, border, pass + 1);
             any[pass] = 1;
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(kFirst64Threads) void k_geo64_first(const PairDev* 
     const int border = visit64<CONN, PHASE, kFirst64Margin, kFirst64Margin, kFirst64Threads>(
         P, tx, ty, S, P.counters + C_GEOERR, kFirst64Rounds);
     if (threadIdx.x == 0) {
-        atomicAdd(&P.counters[C_TILE_VISITS], 1);
+        count_visits(P, tile, 1);
         if (border) {
             mark64<CONN>(P, run, tx, ty, border, 1);
             any[0] = 1;
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256) void k_geo64_finish(const PairDev* __restrict_
             if (threadIdx.x == 0) dirty[tile] = 0u;
             const int border = visit64<CONN, PHASE>(P, tx, ty, S, P.counters + C_GEOERR);
             if (threadIdx.x == 0) {
-                atomicAdd(&P.counters[C_TILE_VISITS], 1);
+                count_visits(P, tile, 1);
                 if (border) {
                     mark64<CONN>(P, run, tx, ty, border, pass + 1);
                     s_any = 1;

@@ -199,6 +199,7 @@ __global__ __launch_bounds__(1024) void k_csr_scan(const PairDev* __restrict__ p
     const int N = P.N;
     const int chunk = ((N + 1023) / 1024 + 3) & ~3;
     const int b = min(N, tid * chunk), e = min(N, b + chunk);
+    const int visits = tid < kVisitWords ? *visit_word(P, tid) : 0;
     u32 sum = 0, dor = 0;    // dor: OR of the degrees (FP32 records hold 16 bits)
     if (e - b == chunk) {
         for (int m = b; m < e; m += 4) {
@@ -242,6 +243,10 @@ __global__ __launch_bounds__(1024) void k_csr_scan(const PairDev* __restrict__ p
     u32 two_e_total = 0;
     for (int w = 0; w < 16; ++w) two_e_total += s_wave[w];
     if (tid == 0) P.row_ptr[N] = two_e_total;
+    if (tid < 64) {
+        const int v = wave::sum(visits);
+        if (tid == 0) P.counters[C_TILE_VISITS] = v;
+    }
     if (tid == 0) {
         const int u = P.counters[C_USED];     // distinct seed pixels (counted by the seeding)
         P.counters[C_DUPLICATE] = N - P.counters[C_OUTSIDE] - u;
