@@ -498,10 +498,11 @@ int run_pairs(epic_ctx* c, const epic_request* reqs, int n, hipStream_t stream, 
                 hi = std::max(hi, hist[k]);
                 lo = std::min(lo, hist[k]);
             }
-        // FP64: when the needs vary, never fewer than the starting budget (its
-        // single-workgroup finisher costs far more than idle passes)
-        const int floor_ = (c->opt.precision == 1 && hi != lo) ? kAutoPassesStart : kAutoPassesMin;
-        return std::min(kMaxPasses - 1, std::max(floor_, hi + (hi == lo ? 0 : 1)));
+        // FP64: two more when the needs vary (its single-workgroup finisher
+        // costs more than idle passes; 16 whenever they vary, as before, was
+        // 14 idle passes a call on 1024 x 436)
+        const int more = hi == lo ? 0 : c->opt.precision == 1 ? 2 : 1;
+        return std::min(kMaxPasses - 1, std::max(kAutoPassesMin, hi + more));
     };
     // With the consistency check (Sec. 5.1) the sequence runs twice: first
     // with NW fits and no assignment, then k_prune compacts the kept matches

@@ -280,13 +280,19 @@ template <int CONN, int PHASE>
 __global__ __launch_bounds__(256) void k_geo64_pass(const PairDev* __restrict__ pairs, RunDev run, int pass) {
     __shared__ Lds64<TW, TH> S;
     int* any = PHASE == 0 ? run.any : run.any2;
-    if (pass > 0 && any[pass - 1] == 0) return;
     // block b takes tile b: the dirty tiles, which cluster in space, are
-    // spread over the XCDs (blocks are dealt to them in turn)
+    // spread over the XCDs (blocks are dealt to them in turn).  Its own flag
+    // is all that gates it (every mark sets its pass's change flag, and the
+    // first pass takes back the seeding's, so after a pass without changes no
+    // tile is marked), read before the bound is tested: the grid is the tile
+    // count rounded up to a multiple of 8, each flag array is carved to a
+    // multiple of 64 entries
     const int tile = (int)blockIdx.x;
-    if (tile >= run.total_tiles) return;
-    u32* dirty = run.dirty[pass & 1];
-    if (dirty[tile] == 0u) return;
+    u32* const d0 = run.dirty[0];
+    u32* const d1 = run.dirty[1];
+    u32* const dirty = (pass & 1) ? d1 : d0;
+    const u32 dflag = dirty[tile];
+    if (tile >= run.total_tiles || dflag == 0u) return;
     const int p = find_pair(run.npairs, tile, [&](int i) { return pairs[i].tile_base; });
     const PairDev& P = pairs[p];
     const int lt = tile - P.tile_base;
@@ -392,14 +398,6 @@ __global__ __launch_bounds__(256) void k_geo64_finish(const PairDev* __restrict_
     if (threadIdx.x == 0) atomicOr(run.error, 1);
 }
 
-// Between the phases: clears the dirty flags the distance phase left.
-__global__ __launch_bounds__(256) void k_geo64_reset(RunDev run) {
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < run.total_tiles; i += gridDim.x * 256) {
-        run.dirty[0][i] = 0u;
-        run.dirty[1][i] = 0u;
-    }
-}
-
 namespace {
 template <int CONN>
 hipError_t launch64_t(const PairDev* d_pairs, const RunDev& run, int passes0, int passes1, hipStream_t s) {
@@ -408,7 +406,8 @@ hipError_t launch64_t(const PairDev* d_pairs, const RunDev& run, int passes0, in
     for (int p = 1; p < passes0; ++p)
         hipLaunchKernelGGL((k_geo64_pass<CONN, 0>), dim3(grid), dim3(256), 0, s, d_pairs, run, p);
     hipLaunchKernelGGL((k_geo64_finish<CONN, 0>), dim3(1), dim3(256), 0, s, d_pairs, run, passes0);
-    hipLaunchKernelGGL(k_geo64_reset, dim3((run.total_tiles + 255) / 256), dim3(256), 0, s, run);
+    // (the distance phase ends with no tile marked, so the label phase starts
+    // on clear flags; its first pass visits every tile anyway)
     hipLaunchKernelGGL((k_geo64_first<CONN, 1>), dim3(grid), dim3(kFirst64Threads), 0, s, d_pairs, run);
     for (int p = 1; p < passes1; ++p)
         hipLaunchKernelGGL((k_geo64_pass<CONN, 1>), dim3(grid), dim3(256), 0, s, d_pairs, run, p);
