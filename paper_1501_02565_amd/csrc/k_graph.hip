@@ -260,6 +260,9 @@ __global__ __launch_bounds__(1024) void k_csr_scan(const PairDev* __restrict__ p
         for (int w = 0; w < 16; ++w) any_big |= s_big[w];
         if (any_big && P.minin64 == nullptr) P.counters[C_OVERFLOW] |= 1;   // a degree above 65535
         if (P.counters[C_OVERFLOW]) status = -6;                       // EPIC_ERR_CAPACITY
+        // in the FP64 path every usable match of an LA pair is fitted in FP64
+        // (unless its search fails, which takes it back)
+        if (P.minin64 && P.mode == 1 && !run.force_nw && !(P.counters[C_OVERFLOW] & 1)) P.counters[C_FP64] = u;
         if ((*run.error & 1) || P.counters[C_GEOERR]) status = -7;     // EPIC_ERR_CONVERGENCE
         if (P.counters[C_BADCOST]) {                                   // EPIC_ERR_COST: not seeded
             status = -8;

@@ -590,7 +590,9 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
             gmem(P.params64)[6LL * s + lane] = v;
         }
         if (lane == 0) {
-            if (la) atomicAdd(&P.counters[C_FP64], 1);
+            // (the FP64 path counts them without an atomic each, which at one
+            // address take 12 ns: the CSR scan sets the count)
+            if (!F64 && la) atomicAdd(&P.counters[C_FP64], 1);
             if (fo.degenerate) atomicAdd(&P.counters[C_DEGENERATE], 1);
         }
     }
@@ -666,7 +668,10 @@ __global__ __launch_bounds__(64) void k_knn_fit_retry(const PairDev* __restrict_
         const int s = gb - P.src_block_base;
         if (!knn_fit_one<VCAP, KMAX, F64>(P, run, s, S)) {
             knn_fit_inactive(P, s);
-            if (threadIdx.x == 0) atomicOr(&P.counters[C_OVERFLOW], 2);
+            if (threadIdx.x == 0) {
+                atomicOr(&P.counters[C_OVERFLOW], 2);
+                if (F64 && P.mode == 1 && !run.force_nw) atomicSub(&P.counters[C_FP64], 1);
+            }
         }
         __syncthreads();
     }
