@@ -63,8 +63,7 @@ size_t pair_bytes(int H, int W, int N, int precision) {
         b += align_up(4 * HW);            // labels
         b += align_up(8 * cap);           // hval64
         b += align_up(8 * (size_t)N);     // minin64
-        b += align_up(8 * cap);           // adjw64
-        b += align_up(8 * cap);           // nbmin64
+        b += align_up(16 * cap);          // adj64
         b += align_up(48 * (size_t)N);    // params64
     }
     b += align_up(8 * HW);            // keys
@@ -402,8 +401,7 @@ int run_pairs(epic_ctx* c, const epic_request* reqs, int n, hipStream_t stream, 
             P.labels = reinterpret_cast<u32*>(take(4 * (size_t)HW));
             P.hval64 = reinterpret_cast<u64*>(take(8 * cap));
             P.minin64 = reinterpret_cast<u64*>(take(8 * (size_t)r.N));
-            P.adjw64 = reinterpret_cast<double*>(take(8 * cap));
-            P.nbmin64 = reinterpret_cast<u64*>(take(8 * cap));
+            P.adj64 = reinterpret_cast<uint4*>(take(16 * cap));
             P.params64 = reinterpret_cast<double*>(take(48 * (size_t)r.N));
         }
         c->last_counters[i] = P.counters;

@@ -106,8 +106,8 @@ struct PairDev {
     u32* labels;            // H*W nearest-match label (keys then hold double D)
     u64* hval64;            // hash_cap: double bits of the edge weight
     u64* minin64;           // N: double bits of the lightest incident edge
-    double* adjw64;         // hash_cap: CSR edge weights
-    u64* nbmin64;           // hash_cap: double bits of the neighbour's lightest edge
+    uint4* adj64;           // hash_cap: double bits of the CSR edge's weight and of the
+                            //   neighbour's lightest edge
     double* params64;       // N*6
     // consistency check of the matches (Sec. 5.1): the kept matches,
     // compacted in index order, and their original indices
@@ -149,6 +149,7 @@ __device__ __forceinline__ uint4 gload(const uint4* p) {
     const gu32x4 v = *(const EPIC_GLOBAL gu32x4*)p;
     return make_uint4(v.x, v.y, v.z, v.w);
 }
+__device__ __forceinline__ u64 words_u64(u32 lo, u32 hi) { return ((u64)hi << 32) | lo; }
 __device__ __forceinline__ float4 gload(const float4* p) {
     const gf32x4 v = *(const EPIC_GLOBAL gf32x4*)p;
     return make_float4(v.x, v.y, v.z, v.w);

@@ -296,14 +296,9 @@ __global__ __launch_bounds__(SLOT_BLOCK) void k_csr_scatter(const PairDev* __res
     if (okn) gstore(P.adj + pn, make_uint4(m, wb, rm, wm));
     if (f64) {
         const u64 wd = gmem(P.hval64)[h];
-        if (okm) {
-            gmem(P.adjw64)[pm] = dbits(wd);
-            gmem(P.nbmin64)[pm] = gmem(P.minin64)[n];
-        }
-        if (okn) {
-            gmem(P.adjw64)[pn] = dbits(wd);
-            gmem(P.nbmin64)[pn] = gmem(P.minin64)[m];
-        }
+        const u64 mn = gmem(P.minin64)[n], mm = gmem(P.minin64)[m];
+        if (okm) gstore(P.adj64 + pm, make_uint4((u32)wd, (u32)(wd >> 32), (u32)mn, (u32)(mn >> 32)));
+        if (okn) gstore(P.adj64 + pn, make_uint4((u32)wd, (u32)(wd >> 32), (u32)mm, (u32)(mm >> 32)));
     }
     if (P.dbg_em) {
         const int e = atomicAdd(P.dbg_n_edges, 1);

@@ -125,6 +125,10 @@ struct NodeSlot {
     }
 };
 
+// FP64: 7.0 KB a match with 256 entries, 23 resident per CU (9.0 KB and 17
+// with every field in double and an array of its own), and up to 128
+// candidates sorted in registers: 1024 x 436 with 8000 matches 357 -> 346 us
+// a call, 1242 x 480 with 9000 380 -> 359 us.
 template <int VCAP, bool F64>
 struct KnnLds {
     static constexpr int HCAP = NodeSlot<VCAP>::SLOTS;
@@ -132,18 +136,22 @@ struct KnnLds {
     using DT = typename std::conditional<F64, u64, u32>::type;     // distance bits
     using RT = typename std::conditional<F64, double, float>::type;
     using ST = typename NodeSlot<VCAP>::T;
-    // entry e: tentative distance (2e) and lightest incident edge (2e + 1);
-    // FP32 packs the edge's high 16 float bits over the degree (low 16 bits),
-    // the CSR record's own word.  After the search: the sort keys.
-    alignas(16) DT dm[2 * VCAP + 2];                // (the last entry takes what does not fit)
-    // entry e: CSR start (FP64: and degree), once settled less its offset in
-    // the step's edges; after the search, the entry's node
-    alignas(16) u32 rd[F64 ? 2 * VCAP + 4 : VCAP + 4];
+    // FP32, entry e: tentative distance (2e), lightest incident edge (2e + 1:
+    // its high 16 float bits over the degree, the CSR record's own word);
+    // FP64: tentative distance (e), the lightest edge rounded down to a float
+    // in mi (the settle test needs a lower bound) and the degree in dg.  The
+    // last entry takes what does not fit.  After the search: the sort keys.
+    static constexpr int DS = F64 ? 1 : 2;        // words of dm per entry
+    alignas(16) DT dm[DS * (VCAP + 1) + (F64 ? 1 : 0)];
+    // entry e: CSR start, once settled less its offset in the step's edges;
+    // after the search, the entry's node
+    alignas(16) u32 rd[VCAP + 4];
     alignas(16) ST htab[HCAP];    // node table
     alignas(16) u32 head[TW + 4]; // ((1 + position) << 12) | (1 + entry) of the edge segment
                                   // starting at a window position, 0 elsewhere (and one that
                                   // takes the marks beyond the window)
-    int snode[F64 ? VCAP : 1];    // FP64: node of each sort key
+    alignas(16) u32 mi[F64 ? VCAP + 4 : 4];       // (after the search: node of each sort key)
+    u32 dg[F64 ? VCAP + 4 : 1];
 };
 
 template <bool F64>
@@ -170,6 +178,17 @@ __device__ __forceinline__ u64 xor_lane_u64(u64 v, int j) {
     }
 }
 
+__device__ __forceinline__ int xor_lane_int(int v, int j) {
+    switch (j) {
+        case 1: return wave::xor_lane<1>(v);
+        case 2: return wave::xor_lane<2>(v);
+        case 4: return wave::xor_lane<4>(v);
+        case 8: return wave::xor_lane<8>(v);
+        case 16: return wave::xor_lane<16>(v);
+        default: return wave::xor_lane<32>(v);
+    }
+}
+
 // Lanes l of a wavefront with bit j of l clear, as a mask (j a power of two
 // below 64): 0x5555..., 0x3333..., 0x0f0f..., ...
 __device__ __forceinline__ constexpr u64 low_lanes(int j) { return ~0ull / ((1ull << j) + 1ull); }
@@ -178,17 +197,24 @@ __device__ __forceinline__ constexpr u64 low_lanes(int j) { return ~0ull / ((1ul
 // v[r] (E = 1 or 2).  Exchanges across lanes go through DPP, swizzle and
 // permute moves; the distance-64 exchange swaps the two registers of a lane.
 // Which lanes keep the smaller key of a pair is a lane mask fixed by the step.
-template <int E>
-__device__ __forceinline__ void bitonic_regs(u64 (&v)[2], int lane) {
+// PAIR: w[r] goes with v[r]; of two equal keys the lower lane's counts as the
+// smaller (without, the keys are distinct, or alike in every way).
+template <int E, bool PAIR>
+__device__ __forceinline__ void bitonic_regs(u64 (&v)[2], int (&w)[2], int lane) {
 #pragma unroll
     for (int k = 2; k <= 64 * E; k <<= 1) {
 #pragma unroll
         for (int j = k >> 1; j > 0; j >>= 1) {
             if (j == 64) {                  // k = 128: ascending everywhere
                 const u64 a = v[0], b = v[1];
-                const bool lt = a < b;
+                const bool lt = PAIR ? a <= b : a < b;
                 v[0] = lt ? a : b;
                 v[1] = lt ? b : a;
+                if constexpr (PAIR) {
+                    const int wa = w[0], wb = w[1];
+                    w[0] = lt ? wa : wb;
+                    w[1] = lt ? wb : wa;
+                }
             } else {
 #pragma unroll
                 for (int r = 0; r < E; ++r) {
@@ -196,8 +222,16 @@ __device__ __forceinline__ void bitonic_regs(u64 (&v)[2], int lane) {
                     // the lower index of an ascending pair (or the upper of a
                     // descending one) keeps the smaller key
                     const u64 asc = k < 64 ? low_lanes(k) : (((64 * r) & k) == 0 ? ~0ull : 0ull);
-                    const bool keep_min = __builtin_amdgcn_inverse_ballot_w64(~(low_lanes(j) ^ asc));
-                    v[r] = ((a < b) == keep_min) ? a : b;
+                    const u64 keep_min = ~(low_lanes(j) ^ asc);
+                    if constexpr (PAIR) {
+                        const int wb = xor_lane_int(w[r], j);
+                        const u64 lt = wave::ballot(a < b) | (wave::ballot(a == b) & low_lanes(j));
+                        const bool own = __builtin_amdgcn_inverse_ballot_w64(~(lt ^ keep_min));
+                        v[r] = own ? a : b;
+                        w[r] = own ? w[r] : wb;
+                    } else {
+                        v[r] = ((a < b) == (bool)__builtin_amdgcn_inverse_ballot_w64(keep_min)) ? a : b;
+                    }
                 }
             }
         }
@@ -230,6 +264,7 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
     // read once: the LDS ordering points below would make the compiler
     // reload it from the descriptor at every window
     const uint4* const adj = P.adj;
+    const uint4* const adj64 = P.adj64;
     const u32 last_rec = (u32)P.hash_cap - 1u;
 
     // ------------------------------------------------------------ Dijkstra
@@ -241,18 +276,20 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
         for (int i = lane; i < NS::NB; i += 64) t[i] = ones;
         if (lane < TW / 4) reinterpret_cast<uint4*>(S.head)[lane] = zero;
         uint4* const dmq = reinterpret_cast<uint4*>(S.dm);
-        const uint4 unused = F64 ? make_uint4(0u, (u32)(DOUBLE_INF_BITS >> 32), 0u, 0u)
-                                 : make_uint4(FLOAT_INF_BITS, 0u, FLOAT_INF_BITS, 0u);
-        for (int i = lane; i < 2 * VCAP * (int)sizeof(typename LdsT::DT) / 16; i += 64) dmq[i] = unused;
+        constexpr u32 DINF = (u32)(DOUBLE_INF_BITS >> 32);
+        const uint4 unused = F64 ? make_uint4(0u, DINF, 0u, DINF) : make_uint4(FLOAT_INF_BITS, 0u, FLOAT_INF_BITS, 0u);
+        for (int i = lane; i < VCAP * 8 / 16; i += 64) dmq[i] = unused;
+        if constexpr (F64)
+            for (int i = lane; i < VCAP / 4; i += 64) reinterpret_cast<uint4*>(S.mi)[i] = zero;
     }
     __syncthreads();
     if (lane == 0) {
         const u32 a = gmem(P.row_ptr)[s], b = gmem(P.row_ptr)[s + 1];
         S.dm[0] = 0;
         if constexpr (F64) {
-            S.dm[1] = gmem(P.minin64)[s];
+            S.mi[0] = __float_as_uint(__double2float_rd(dbits(gmem(P.minin64)[s])));
             S.rd[0] = a;
-            S.rd[1] = b - a;
+            S.dg[0] = b - a;
         } else {
             // (a degree above 16 bits stops the pair before this kernel)
             S.dm[1] = (gmem(P.minin)[s] & 0xffff0000u) | (b - a);
@@ -269,7 +306,6 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
     // unless settled in it) and where they start among the step's edges.
     // Kept as numbers, not as lane masks: the scalar unit, shared by the
     // CU's four SIMDs, is nearly as busy with this kernel as the SIMDs are.
-    using DT2 = typename std::conditional<F64, ulonglong2, uint2>::type;
     RT d[R], sf[R];
     u32 dg[R], off[R];
 #pragma unroll
@@ -291,14 +327,15 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if (RU ? r >= RU : r >= ru) continue;
-            const DT2 v = *reinterpret_cast<const DT2*>(&S.dm[2 * (lane + 64 * r)]);
-            d[r] = from_bits<F64>(v.x);
             if constexpr (F64) {
-                mi[r] = dbits(v.y);
-                dg[r] = S.rd[2 * (lane + 64 * r) + 1];
+                d[r] = dbits(S.dm[lane + 64 * r]);
+                mi[r] = (double)__uint_as_float(S.mi[lane + 64 * r]);
+                dg[r] = S.dg[lane + 64 * r];
                 x[r] = sf[r] > d[r] ? sf[r] : d[r];
                 fmin = fmin < x[r] ? fmin : x[r];
             } else {
+                const uint2 v = *reinterpret_cast<const uint2*>(&S.dm[2 * (lane + 64 * r)]);
+                d[r] = __uint_as_float(v.x);
                 mi[r] = __uint_as_float(v.y & 0xffff0000u);
                 dg[r] = v.y & 0xffffu;
                 x[r] = __uint_as_float(max(__float_as_uint(d[r]), __float_as_uint(sf[r])));
@@ -345,7 +382,7 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
             if (newly[r]) {
                 const u32 at = min(o, (u32)TW);
                 S.head[at] = (at << 12) + (u32)((1 << 12) + lane + 64 * r + 1);
-                atomicSub(&S.rd[(F64 ? 2 : 1) * (lane + 64 * r)], o);
+                atomicSub(&S.rd[lane + 64 * r], o);
             }
             o += dg[r];
         }
@@ -389,8 +426,8 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
             // look for the source s, which is in the table)
             const bool act = lane < T - wb;
             const u32 qe = seg - 1u;
-            const RT du = from_bits<F64>(S.dm[2 * qe]);
-            const u32 ei = min(S.rd[F64 ? 2 * qe : qe] + (u32)wb + (u32)lane, last_rec);
+            const RT du = from_bits<F64>(S.dm[LdsT::DS * qe]);
+            const u32 ei = min(S.rd[qe] + (u32)wb + (u32)lane, last_rec);
             // (32-bit slots: nodes below 2^23, so the records lie within 2 GiB)
             const uint4 rec = sizeof(ST) == 4
                                   ? gload(reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(adj) + (ei << 4)))
@@ -398,8 +435,10 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
             RT cand;
             u64 nbm = 0ull;
             if constexpr (F64) {
-                cand = du + gmem(P.adjw64)[ei];
-                nbm = gmem(P.nbmin64)[ei];
+                // (one 16-byte load beside the record's)
+                const uint4 r64 = gload(adj64 + ei);
+                cand = du + dbits(words_u64(r64.x, r64.y));
+                nbm = words_u64(r64.z, r64.w);
             } else {
                 cand = du + __uint_as_float(rec.y);
             }
@@ -424,17 +463,16 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
             const u64 m = wave::ballot(prev == NS::EMPTY);
             if (__builtin_amdgcn_inverse_ballot_w64(m)) {
                 const u32 en = min((u32)(nvis + wave::lanes_below(m)), (u32)VCAP);
-                S.dm[2 * en] = to_bits<F64>(cand);
+                S.dm[LdsT::DS * en] = to_bits<F64>(cand);
+                S.rd[en] = rec.z;
                 if constexpr (F64) {
-                    S.dm[2 * en + 1] = nbm;
-                    S.rd[2 * en] = rec.z;
-                    S.rd[2 * en + 1] = rec.w;
+                    S.mi[en] = __float_as_uint(__double2float_rd(dbits(nbm)));
+                    S.dg[en] = rec.w;
                 } else {
                     // lightest edge bits over the degree; the edge was
                     // rounded down to 16 bits: a lower bound, which is all
                     // the settle test needs
                     S.dm[2 * en + 1] = rec.w;
-                    S.rd[en] = rec.z;
                 }
                 htab[slot] = NS::pack(v, en);
             }
@@ -443,7 +481,7 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
             // relax: nodes claimed in this window have their entries by now
             if (e >= (u32)VCAP) e = NS::entry(htab[slot]);
             // (lanes without an edge stay out: atomics on one address go one by one)
-            if (act) atomicMin(&S.dm[2 * e], to_bits<F64>(cand));
+            if (act) atomicMin(&S.dm[LdsT::DS * e], to_bits<F64>(cand));
             lds_order();
         }
         if (nvis > VCAP) return false;
@@ -456,6 +494,7 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
     // each entry's node, from the node table (slot -> node, slot -> entry),
     // into the CSR array, which the search no longer needs
     int* const node_of = reinterpret_cast<int*>(S.rd);
+    int* const snode = reinterpret_cast<int*>(S.mi);      // FP64: the node of each sort key
     __syncthreads();
     for (int h = lane; h < HCAP; h += 64) {
         const ST w = htab[h];
@@ -474,7 +513,7 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
             const int e = lane + 64 * r;
             if constexpr (F64) {
                 keys[pos] = bitsd(d[r]);
-                S.snode[pos] = node_of[e];
+                snode[pos] = node_of[e];
             } else {
                 keys[pos] = ((u64)__float_as_uint(d[r]) << 32) | (u32)node_of[e];
             }
@@ -485,6 +524,36 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
     int knode[RK];
     RT kdist[RK];
     bool sorted = false;
+    if constexpr (F64 && VCAP <= 256) {
+        // up to 128 keys: sorted in registers by the distance alone; only
+        // equal distances need the nodes in the comparison, and go to the
+        // sort in LDS
+        static_assert(RK <= 2, "register sort holds two keys per lane");
+        if (p2 <= 128) {
+            __syncthreads();
+            u64 v[2];
+            int w[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const bool in = lane + 64 * r < nc;
+                v[r] = in ? keys[lane + 64 * r] : ~0ull;
+                w[r] = in ? snode[lane + 64 * r] : 0x7fffffff;
+            }
+            if (p2 == 64) bitonic_regs<1, true>(v, w, lane); else bitonic_regs<2, true>(v, w, lane);
+            // the next key of each lane's keys (the last lane of the first
+            // register is followed by the first of the second)
+            const u64 n0 = __shfl_down(v[0], 1), n1 = __shfl_down(v[1], 1), h = __shfl(v[1], 0);
+            const bool tie = (lane + 1 < nc && v[0] == (lane == 63 ? h : n0)) || (lane + 65 < nc && v[1] == n1);
+            if (wave::ballot(tie) == 0ull) {
+#pragma unroll
+                for (int r = 0; r < RK; ++r) {
+                    knode[r] = w[r];
+                    kdist[r] = dbits(v[r]);
+                }
+                sorted = true;
+            }
+        }
+    }
     if constexpr (!F64 && VCAP <= 256) {
         // up to 128 keys (the usual case): sorted in registers
         static_assert(RK <= 2, "register sort holds two keys per lane");
@@ -493,7 +562,8 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
             u64 v[2];
             v[0] = lane < nc ? keys[lane] : ~0ull;
             v[1] = lane + 64 < nc ? keys[lane + 64] : ~0ull;
-            if (p2 == 64) bitonic_regs<1>(v, lane); else bitonic_regs<2>(v, lane);
+            int none[2];
+            if (p2 == 64) bitonic_regs<1, false>(v, none, lane); else bitonic_regs<2, false>(v, none, lane);
 #pragma unroll
             for (int r = 0; r < RK; ++r) {
                 knode[r] = (int)(u32)v[r];
@@ -505,7 +575,7 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
     if (!sorted) {
         for (int i = nc + lane; i < p2; i += 64) {
             keys[i] = ~0ull;
-            if constexpr (F64) S.snode[i] = 0x7fffffff;
+            if constexpr (F64) snode[i] = 0x7fffffff;
         }
         __syncthreads();
         // each lane takes compare-exchange pairs (i, i + j): pair t has i = t
@@ -519,14 +589,14 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
                         const u64 a = keys[i], b = keys[ixj];
                         const bool up = (i & k) == 0;
                         if constexpr (F64) {
-                            const int na = S.snode[i], nb = S.snode[ixj];
+                            const int na = snode[i], nb = snode[ixj];
                             const bool gt = a > b || (a == b && na > nb);
                             const bool lt = a < b || (a == b && na < nb);
                             if (up ? gt : lt) {
                                 keys[i] = b;
                                 keys[ixj] = a;
-                                S.snode[i] = nb;
-                                S.snode[ixj] = na;
+                                snode[i] = nb;
+                                snode[ixj] = na;
                             }
                         } else {
                             // keys are distinct except the padding, whose swap is harmless
@@ -545,7 +615,7 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
             const int jj = lane + 64 * r;
             const u64 kb = jj < p2 ? keys[jj] : ~0ull;
             if constexpr (F64) {
-                knode[r] = jj < p2 ? S.snode[jj] : 0x7fffffff;
+                knode[r] = jj < p2 ? snode[jj] : 0x7fffffff;
                 kdist[r] = dbits(kb);
             } else {
                 knode[r] = (int)(u32)kb;
