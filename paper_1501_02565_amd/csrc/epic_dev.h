@@ -355,7 +355,33 @@ struct ExactArgs {
     int mode, wpow;
     float fp64_route;
     double deg_tau;
+    // the per-source path (null / 0 in the other)
+    float2* cu;             // H*W: cost and ubound
+    u32* ctl;               // X_WORDS
+    u32* pend[2];           // N each: sources put off, by round parity
+    u32* big;               // N: sources that outgrew LDS
+    u32* bcount;            // entries of each 8 x 8 block
+    u32* offset;            // their prefix sums
+    uint4* meta;            // pool_cap: an entry's block, rank in it and source
+    uint2* order;           // pool_cap: the blocks' entries, (entry, source)
+    u32* pool;              // pool_cap * 64: an entry's distance bits
+    u32* scratch;           // pages of the sources that outgrew LDS, per workgroup
+    size_t scratch_words;
+    u32 pool_cap;
+    int round;
 };
+// Control words of the per-source path (each in a cache line of its own).
+enum : int {
+    X_USED = 0,             // entries asked for
+    X_LIMIT = 16,           // entries before this one are whole (the pool's end, or the
+                            //   first that did not fit)
+    X_BIG = 32,             // sources that outgrew LDS
+    X_PEND0 = 48,           // sources put off to an even round; odd: 16 words on
+    X_WORDS = 80
+};
+// One workgroup per source (k_exact_reach.hip), in up to `rounds` rounds;
+// big_groups workgroups for the sources that outgrow LDS.
+hipError_t launch_exact_reach(const ExactArgs& A, int conn, int rounds, int big_groups, hipStream_t s);
 hipError_t launch_exact_owner(const PairDev* full, const ExactArgs& A, hipStream_t s);
 hipError_t launch_exact_select(const PairDev* chunk, int nsrc, int src0, int first, int last, const ExactArgs& A,
                                hipStream_t s);

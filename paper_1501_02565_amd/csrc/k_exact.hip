@@ -18,6 +18,8 @@
 // matches that hold their pixel (placed, lowest index), so dropped and
 // duplicate matches never enter a list.  k_exact_fit then fits each pixel
 // (fit.h) with the pixel as the anchor.
+// This form serves small workspaces; given room, k_exact_reach.hip takes the
+// steps after the bounds.
 #include "epic_dev.h"
 #include "fit.h"
 #include "wave.h"
@@ -44,6 +46,7 @@ __global__ __launch_bounds__(256) void k_exact_bound(const PairDev* __restrict__
         if (A.knn_idx[j] >= 0) u = (key_dist(k) + A.knn_d[j]) * 1.001f + 1e-6f;
     }
     A.ubound[p] = u;
+    if (A.cu) gstore(A.cu + p, make_float2(gmem(P.cost)[p], u));
 }
 
 __global__ __launch_bounds__(256) void k_exact_owner(const PairDev* __restrict__ full, ExactArgs A) {
