@@ -400,10 +400,9 @@ struct VarArgs {
     const float* u0;        // H*W*2, the field to refine
     float* flow;            // H*W*2 output (may equal u0)
     float* I2w;             // H*W*C scratch: I2 warped by u0
-    float* coef;            // 13 planes of H*W: JC (6), JG (6), alpha
-    float* sys;             // 9 planes of H*W: a fixed-point step's per-pixel update
-    float* du[2];           // H*W each, a ping-pong pair
-    float* dv[2];
+    float* coef;            // JC (6) and JG (6) in 3 planes of float4 of H*W, then alpha, H*W
+    float* sys;             // 2 planes of float4 of H*W: a fixed-point step's per-pixel update
+    float2* d[2];           // (du, dv), H*W each, a ping-pong pair
     int H, W, C;
     long long HW;
     float lam, delta, gamma, kappa, eps, zeta, omega;

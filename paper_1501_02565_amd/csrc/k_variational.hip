@@ -29,25 +29,24 @@
 // Kernels (FP32):
 //   k_var_warp     I2w (pixel-parallel)
 //   k_var_coef     per pixel the colour and gradient systems J (6 entries
-//                  each) and alpha, stored as 13 planes
-//   k_var_weights  per fixed-point step and pixel the 9 numbers its update
+//                  each) and alpha, stored as 3 planes of 16-byte records and one
+//   k_var_weights  per fixed-point step and pixel the numbers its update
 //                  needs: omega / D1 and omega / D2 for the diagonals
 //                  D1 = A11 + sum g, D2 = A22 + sum g (one division per
 //                  step, not per sweep), A12, right-hand sides B1, B2, and
-//                  its 4 edge weights
-//                  (each edge evaluated in one canonical order, so both
-//                  endpoints hold the same value)
-//   k_var_sor      S half-sweeps per launch with the sweeps blocked in time:
-//                  a workgroup loads its tile and a halo of S pixels into
-//                  LDS (du, dv, the two colours in separate arrays) and its
-//                  pixels' 9 numbers into registers, relaxes the whole
-//                  region S times (each half-sweep corrupts at most one
-//                  more ring from the region's edge inwards, so the tile's
-//                  values equal those of S global half-sweeps) and writes
-//                  the tile to the other buffer of a ping-pong pair.  A
+//                  its edge weights (each edge evaluated in one canonical
+//                  order, so both endpoints see the same value), in two
+//                  records of 16 bytes
+//   k_var_sor      up to 16 half-sweeps per launch with the sweeps blocked
+//                  in time: a workgroup loads its tile and a halo of 16
+//                  pixels, relaxes the whole region (each half-sweep
+//                  corrupts at most one more ring from the region's edge
+//                  inwards, so the tile's values equal those of global
+//                  half-sweeps) and writes the tile to the other buffer of
+//                  a ping-pong pair, the last launch u0 + du instead.  A
 //                  launch per half-sweep would spend most of its time in
 //                  launching and in re-reading the system from memory.
-//   k_var_out      u0 + du
+//   k_var_copy     u0, for a call without sweeps
 #include <type_traits>
 
 #include "epic_dev.h"
@@ -121,35 +120,59 @@ __global__ __launch_bounds__(256) void k_var_coef(VarArgs A) {
         J[11] += thx * Ixz * Ixz + thy * Iyz * Iyz;
         gn += gx1 * gx1 + gy1 * gy1;
     }
-    for (int k = 0; k < 12; ++k) A.coef[(long long)k * A.HW + i] = J[k];
+    float4* S = reinterpret_cast<float4*>(A.coef);
+    S[i] = make_float4(J[0], J[1], J[2], J[3]);
+    S[A.HW + i] = make_float4(J[4], J[5], J[6], J[7]);
+    S[2 * A.HW + i] = make_float4(J[8], J[9], J[10], J[11]);
     A.coef[12LL * A.HW + i] = expf(-A.kappa * sqrtf(gn));
+    A.d[0][i] = make_float2(0.0f, 0.0f);
+}
+
+// The input field's two numbers at pixel i in one load (the field need only be
+// aligned to a float).
+struct __attribute__((packed, aligned(4))) Flow2 { float u, v; };
+__device__ __forceinline__ float2 field(const float* f, long long i) {
+    const Flow2 t = reinterpret_cast<const Flow2*>(f)[i];
+    return make_float2(t.u, t.v);
+}
+
+// A pixel as the smoothness weights see it: alpha, (u0, v0) and (du, dv).
+struct VarPixel {
+    float alpha;
+    float2 u, d;
+};
+
+__device__ __forceinline__ VarPixel var_pixel(const VarArgs& A, const float2* d, long long i) {
+    return {A.coef[12LL * A.HW + i], field(A.u0, i), d[i]};
 }
 
 // Edge (p, q) with p the left or upper pixel: lam (alpha_p + alpha_q) / 2
 // psi'(|U_q - U_p|^2 + |V_q - V_p|^2), in this one order for both ends.
-__device__ __forceinline__ float edge_weight(const VarArgs& A, const float* du, const float* dv, long long p,
-                                             long long q) {
-    const float* alpha = A.coef + 12LL * A.HW;
-    const float dU = (A.u0[2 * q] + du[q]) - (A.u0[2 * p] + du[p]);
-    const float dV = (A.u0[2 * q + 1] + dv[q]) - (A.u0[2 * p + 1] + dv[p]);
-    return A.lam * 0.5f * (alpha[p] + alpha[q]) * psi_d(dU * dU + dV * dV, A.eps);
+__device__ __forceinline__ float edge_weight(const VarArgs& A, const VarPixel& p, const VarPixel& q) {
+    const float dU = (q.u.x + q.d.x) - (p.u.x + p.d.x);
+    const float dV = (q.u.y + q.d.y) - (p.u.y + p.d.y);
+    return A.lam * 0.5f * (p.alpha + q.alpha) * psi_d(dU * dU + dV * dV, A.eps);
 }
 
-// planes of A.sys
-enum { S_W1, S_W2, S_A12, S_B1, S_B2, S_GL, S_GR, S_GU, S_GD, S_NPLANES };
-
-__global__ __launch_bounds__(256) void k_var_weights(VarArgs A, const float* __restrict__ du,
-                                                     const float* __restrict__ dv) {
+// A pixel's update, two records of A.sys:
+//   [i]       omega / D1, omega / D2 (0 for an empty equation, which keeps
+//             its unknown), A12, B1
+//   [HW + i]  B2 and the weights of its right, lower and left edge (the
+//             upper edge is the lower one of the pixel above)
+__global__ __launch_bounds__(256) void k_var_weights(VarArgs A, const float2* __restrict__ d) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= A.HW) return;
     const int W = A.W, H = A.H;
     const int x = (int)(i % W), y = (int)(i / W);
-    float JC[6], JG[6];
-    for (int k = 0; k < 6; ++k) {
-        JC[k] = A.coef[(long long)k * A.HW + i];
-        JG[k] = A.coef[(long long)(6 + k) * A.HW + i];
-    }
-    const float dui = du[i], dvi = dv[i];
+    const float4* S = reinterpret_cast<const float4*>(A.coef);
+    const float4 s0 = S[i], s1 = S[A.HW + i], s2 = S[2 * A.HW + i];
+    const float JC[6] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y};
+    const float JG[6] = {s1.z, s1.w, s2.x, s2.y, s2.z, s2.w};
+    // a neighbour outside the image: the pixel itself (its weight is not used)
+    const VarPixel P = var_pixel(A, d, i);
+    const VarPixel Pl = var_pixel(A, d, x > 0 ? i - 1 : i), Pr = var_pixel(A, d, x + 1 < W ? i + 1 : i);
+    const VarPixel Pu = var_pixel(A, d, y > 0 ? i - W : i), Pd = var_pixel(A, d, y + 1 < H ? i + W : i);
+    const float dui = P.d.x, dvi = P.d.y;
     const float wc = A.delta * psi_d(quad(JC, dui, dvi), A.eps);
     const float wg = A.gamma * psi_d(quad(JG, dui, dvi), A.eps);
     const float a11 = wc * JC[0] + wg * JG[0];
@@ -159,197 +182,201 @@ __global__ __launch_bounds__(256) void k_var_weights(VarArgs A, const float* __r
     float b2 = -(wc * JC[4] + wg * JG[4]);
     // the 4 edges (0 where there is no neighbour) and the fixed part of the
     // neighbour sums, sum_j g (u0_j - u0_i)
-    const float gl = x > 0 ? edge_weight(A, du, dv, i - 1, i) : 0.0f;
-    const float gr = x + 1 < W ? edge_weight(A, du, dv, i, i + 1) : 0.0f;
-    const float gu = y > 0 ? edge_weight(A, du, dv, i - W, i) : 0.0f;
-    const float gd = y + 1 < H ? edge_weight(A, du, dv, i, i + W) : 0.0f;
-    const float u0i = A.u0[2 * i], v0i = A.u0[2 * i + 1];
-    auto fold = [&](float g, long long j) {
-        b1 += g * (A.u0[2 * j] - u0i);
-        b2 += g * (A.u0[2 * j + 1] - v0i);
+    const float gl = x > 0 ? edge_weight(A, Pl, P) : 0.0f;
+    const float gr = x + 1 < W ? edge_weight(A, P, Pr) : 0.0f;
+    const float gu = y > 0 ? edge_weight(A, Pu, P) : 0.0f;
+    const float gd = y + 1 < H ? edge_weight(A, P, Pd) : 0.0f;
+    auto fold = [&](float g, const VarPixel& q) {
+        b1 += g * (q.u.x - P.u.x);
+        b2 += g * (q.u.y - P.u.y);
     };
-    if (x > 0) fold(gl, i - 1);
-    if (x + 1 < W) fold(gr, i + 1);
-    if (y > 0) fold(gu, i - W);
-    if (y + 1 < H) fold(gd, i + W);
+    if (x > 0) fold(gl, Pl);
+    if (x + 1 < W) fold(gr, Pr);
+    if (y > 0) fold(gu, Pu);
+    if (y + 1 < H) fold(gd, Pd);
     const float sw = ((gl + gr) + gu) + gd;
-    float* P = A.sys;
-    const long long HW = A.HW;
-    // omega over the diagonal (0 for an empty equation, which keeps its
-    // unknown)
     const float d1 = a11 + sw, d2 = a22 + sw;
-    P[S_W1 * HW + i] = d1 > 0.0f ? A.omega / d1 : 0.0f;
-    P[S_W2 * HW + i] = d2 > 0.0f ? A.omega / d2 : 0.0f;
-    P[S_A12 * HW + i] = a12;
-    P[S_B1 * HW + i] = b1;
-    P[S_B2 * HW + i] = b2;
-    P[S_GL * HW + i] = gl;
-    P[S_GR * HW + i] = gr;
-    P[S_GU * HW + i] = gu;
-    P[S_GD * HW + i] = gd;
+    float4* R = reinterpret_cast<float4*>(A.sys);
+    R[i] = make_float4(d1 > 0.0f ? A.omega / d1 : 0.0f, d2 > 0.0f ? A.omega / d2 : 0.0f, a12, b1);
+    R[A.HW + i] = make_float4(b2, gr, gd, gl);
 }
 
-#ifndef EPIC_VAR_TX
-#define EPIC_VAR_TX 64
-#endif
-#ifndef EPIC_VAR_TY
-#define EPIC_VAR_TY 32
-#endif
-#ifndef EPIC_VAR_S
-#define EPIC_VAR_S 12
-#endif
-#ifndef EPIC_VAR_NT
-#define EPIC_VAR_NT 512
-#endif
+// The sweeps' tile: TX x TY pixels and a halo of S (the most half-sweeps a
+// launch runs; even, so every launch starts with red) make the region RX x RY
+// of NR strips of KP rows.  Thread (strip, s) holds pixels 2s and 2s + 1 of
+// its strip's rows -- one of each colour per row -- with their update records
+// in registers.  All tile and strip edges are even, so which of the two is
+// red is known at compile time, and of a pixel's four neighbours the other
+// one of its pair and, inside the strip, the ones above and below are the
+// thread's own registers: 1 + 2 / KP instead of 4 LDS reads per update.  An
+// edge between two pixels of a thread is held once.  A wave whose rows can no
+// longer reach the tile in the sweeps that are left skips them.
+//
+// What bounds it: 16 half-sweeps take 6.3 of a launch's 15 us at 1024 x 436
+// (FP32 FMAs and a barrier each), the records 1.4 (2 x 16 bytes a pixel), and
+// most of the rest is the launch itself, so a launch runs 16 (S = 20 saves a
+// quarter of the launches and gives it back in halo: 364 against 359 us a call
+// with 64 x 28 tiles).  With records in nine planes, all four neighbours from
+// LDS, S = 12 and 64 x 32 tiles a call took 626 us; now 359.
+template <int TX_, int S_, int KP_, int NR_>
+struct VarTile {
+    static constexpr int TX = TX_, S = S_, KP = KP_, NR = NR_;
+    static_assert(TX % 2 == 0 && S % 2 == 0 && KP % 2 == 0, "even tile width, halo and strip");
+    static constexpr int RX = TX + 2 * S, RY = NR * KP, TY = RY - 2 * S, RXh = RX / 2;
+    static constexpr int NT = (NR * RXh + 63) / 64 * 64;
+    static_assert(TY > 0 && NT <= 1024, "tile");
+    static long long tiles(int H, int W) { return (long long)((W + TX - 1) / TX) * ((H + TY - 1) / TY); }
+};
+// 32 x 32 pixels, 1024 threads of 2 rows: two workgroups fit a CU.  64 x 28
+// pixels, 720 threads of 4 rows: one per CU, and a third less halo.
+using VarSmall = VarTile<32, 16, 2, 32>;
+using VarWide = VarTile<64, 16, 4, 15>;
+constexpr int kVarCus = 256;
 
-// Tile TX x TY, halo S (= the most half-sweeps a launch runs; even, so every
-// launch starts with red), NT threads.  The region RX x RY = (TX + 2S) x
-// (TY + 2S) holds RX/2 pixels of each colour per row; slot s of colour c
-// in region row y is the pixel x = 2s + ((c + X0 + Y0 + y) & 1).  In LDS
-// each colour is a padded (RY + 2) x (RX/2 + 2) array of (du, dv): the
-// neighbours of slot s (colour c, row y, parity p) are, in the other
-// colour's array, slots s - 1 + p and s + p of row y and slot s of rows
-// y - 1 and y + 1 -- consecutive lanes read consecutive words.
-template <int TX, int TY, int S, int NT>
-__global__ __launch_bounds__(NT) void k_var_sor(VarArgs A, const float* __restrict__ du_in,
-                                                const float* __restrict__ dv_in, float* __restrict__ du_out,
-                                                float* __restrict__ dv_out, int nh) {
-    static_assert(S % 2 == 0 && TX % 2 == 0, "even halo and tile width");
-    constexpr int RX = TX + 2 * S, RY = TY + 2 * S, RXh = RX / 2, NS = RY * RXh;
-    constexpr int KP = (NS + NT - 1) / NT;
+template <class T>
+__global__ __launch_bounds__(T::NT) void k_var_sor(VarArgs A, const float2* __restrict__ in, float2* __restrict__ out,
+                                                   int nh, int last) {
+    constexpr int TX = T::TX, S = T::S, KP = T::KP, NR = T::NR, RY = T::RY, TY = T::TY, RXh = T::RXh, NT = T::NT;
     constexpr int LW = RXh + 2, LN = (RY + 2) * LW;
     __shared__ float2 L[2][LN];
     const int tid = threadIdx.x;
     const int W = A.W, H = A.H;
-    const long long HW = A.HW;
     const int tiles_x = (W + TX - 1) / TX;
     const int X0 = (int)(blockIdx.x % tiles_x) * TX - S, Y0 = (int)(blockIdx.x / tiles_x) * TY - S;
-    for (int k = tid; k < 2 * LN; k += NT) (&L[0][0])[k] = make_float2(0.0f, 0.0f);
-    __syncthreads();
-    // this thread's slots: the 9 numbers, its own (du, dv), the LDS cells
-    float cf[2][KP][S_NPLANES];
-    float2 own[2][KP];
-    int cell[2][KP], par[2][KP];
+    // the pads around the region: read by its outermost ring only
+    for (int k = tid; k < 2 * (2 * LW + 2 * RY); k += NT) {
+        const int a = k & 1, q = k >> 1;
+        const int e = q < LW ? q : q < 2 * LW ? (RY + 1) * LW + q - LW
+                                              : (1 + (q - 2 * LW) / 2) * LW + ((q & 1) ? LW - 1 : 0);
+        L[a][e] = make_float2(0.0f, 0.0f);
+    }
+    const int strip = tid / RXh, s = tid % RXh, y0 = strip * KP;
+    const bool act = strip < NR;
+    const int cell = (y0 + 1) * LW + s + 1;
+    const float4* R = reinterpret_cast<const float4*>(A.sys);
+    // this thread's pixels [row][x & 1]
+    float2 v[KP][2];
+    float w1[KP][2], w2[KP][2], a12[KP][2], b1[KP][2], b2[KP][2], gr[KP][2], gd[KP][2], gl[KP], gu[2] = {0.0f, 0.0f};
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
+    for (int k = 0; k < KP; ++k) {
 #pragma unroll
-        for (int k = 0; k < KP; ++k) {
-            const int slot = tid + k * NT;
-            const int y = slot / RXh, s = slot % RXh;
-            const int p = (c + X0 + Y0 + y) & 1;
-            const int gx = X0 + 2 * s + p, gy = Y0 + y;
-            // slots past the region park on a harmless cell (they never
-            // update: W = 0, and their writes are skipped)
-            cell[c][k] = slot < NS ? (y + 1) * LW + s + 1 : LW + 1;
-            par[c][k] = p;
-            own[c][k] = make_float2(0.0f, 0.0f);
-#pragma unroll
-            for (int q = 0; q < S_NPLANES; ++q) cf[c][k][q] = 0.0f;   // W = 0: never updated
-            if (slot < NS && gx >= 0 && gx < W && gy >= 0 && gy < H) {
+        for (int p = 0; p < 2; ++p) {
+            const int y = y0 + k, gx = X0 + 2 * s + p, gy = Y0 + y;
+            float4 r0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), r1 = r0;
+            v[k][p] = make_float2(0.0f, 0.0f);
+            // rows past the reach of this launch's sweeps are not needed
+            if (act && y >= S - nh && y < RY - S + nh && gx >= 0 && gx < W && gy >= 0 && gy < H) {
                 const long long i = (long long)gy * W + gx;
-#pragma unroll
-                for (int q = 0; q < S_NPLANES; ++q) cf[c][k][q] = A.sys[q * HW + i];
-                own[c][k] = make_float2(du_in[i], dv_in[i]);
-                L[c][cell[c][k]] = own[c][k];
+                r0 = R[i];
+                r1 = R[A.HW + i];
+                v[k][p] = in[i];
+                if (k == 0 && gy > 0) gu[p] = R[A.HW + i - W].z;
             }
+            w1[k][p] = r0.x; w2[k][p] = r0.y; a12[k][p] = r0.z; b1[k][p] = r0.w;
+            b2[k][p] = r1.x; gr[k][p] = r1.y; gd[k][p] = r1.z;
+            if (p == 0) gl[k] = r1.w;
+            if (act) L[p][cell + k * LW] = v[k][p];
         }
     }
     __syncthreads();
     const float om1 = 1.0f - A.omega;
-    // one half-sweep over colour C (a compile-time colour: the register
-    // arrays are indexed by constants only)
-    auto half = [&](auto colour) {
+    // the rows of this wave
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wy0 = wave * 64 / RXh * KP, wy1 = min((wave * 64 + 63) / RXh, NR - 1) * KP + KP;
+    auto half = [&](auto colour, int left) {
         constexpr int c = decltype(colour)::value;
-        const float2* N = L[c ^ 1];
-        // all neighbour reads first (this half-sweep writes only colour c),
-        // so the reads of every slot are in flight together
-        float2 nb[KP][4];
+        // rows within `left` half-sweeps' reach of the tile
+        if (wy1 > S - left && wy0 < RY - S + left && act) {
+            float2 far[KP], up, dn;
 #pragma unroll
-        for (int k = 0; k < KP; ++k) {
-            const int e = cell[c][k], p = par[c][k];
-            nb[k][0] = N[e - 1 + p];
-            nb[k][1] = N[e + p];
-            nb[k][2] = N[e - LW];
-            nb[k][3] = N[e + LW];
+            for (int k = 0; k < KP; ++k) far[k] = (c + k) & 1 ? L[0][cell + k * LW + 1] : L[1][cell + k * LW - 1];
+            up = L[c][cell - LW];
+            dn = L[(c + KP - 1) & 1][cell + KP * LW];
+#pragma unroll
+            for (int k = 0; k < KP; ++k) {
+                const int p = (c + k) & 1;
+                const float2 l = p ? v[k][0] : far[k], r = p ? far[k] : v[k][1];
+                const float2 u = k ? v[k - (k > 0)][p] : up, d = k < KP - 1 ? v[k + (k < KP - 1)][p] : dn;
+                const float g0 = p ? gr[k][0] : gl[k], g2 = k ? gd[k - (k > 0)][p] : gu[p];
+                // every rounding spelled out, so the result does not depend on
+                // how the compiler schedules (and fuses) the unrolled slots:
+                // any tiling gives the same bits
+                const float su = __fmaf_rn(gd[k][p], d.x, __fmaf_rn(g2, u.x, __fmaf_rn(gr[k][p], r.x,
+                                                                                       __fmul_rn(g0, l.x))));
+                const float sv = __fmaf_rn(gd[k][p], d.y, __fmaf_rn(g2, u.y, __fmaf_rn(gr[k][p], r.y,
+                                                                                       __fmul_rn(g0, l.y))));
+                float2 t = v[k][p];
+                if (w1[k][p] > 0.0f)
+                    t.x = __fmaf_rn(__fadd_rn(__fmaf_rn(-a12[k][p], t.y, b1[k][p]), su), w1[k][p], __fmul_rn(om1, t.x));
+                if (w2[k][p] > 0.0f)
+                    t.y = __fmaf_rn(__fadd_rn(__fmaf_rn(-a12[k][p], t.x, b2[k][p]), sv), w2[k][p], __fmul_rn(om1, t.y));
+                v[k][p] = t;
+                L[p][cell + k * LW] = t;
+            }
         }
-#pragma unroll
-        for (int k = 0; k < KP; ++k) {
-            const float* f = cf[c][k];
-            const float2 l = nb[k][0], r = nb[k][1], u = nb[k][2], d = nb[k][3];
-            // every rounding spelled out, so the result does not depend on
-            // how the compiler schedules (and fuses) the unrolled slots:
-            // any tiling gives the same bits
-            const float su = __fmaf_rn(f[S_GD], d.x, __fmaf_rn(f[S_GU], u.x, __fmaf_rn(f[S_GR], r.x,
-                                                                                        __fmul_rn(f[S_GL], l.x))));
-            const float sv = __fmaf_rn(f[S_GD], d.y, __fmaf_rn(f[S_GU], u.y, __fmaf_rn(f[S_GR], r.y,
-                                                                                        __fmul_rn(f[S_GL], l.y))));
-            float2 v = own[c][k];
-            if (f[S_W1] > 0.0f)
-                v.x = __fmaf_rn(__fadd_rn(__fmaf_rn(-f[S_A12], v.y, f[S_B1]), su), f[S_W1], __fmul_rn(om1, v.x));
-            if (f[S_W2] > 0.0f)
-                v.y = __fmaf_rn(__fadd_rn(__fmaf_rn(-f[S_A12], v.x, f[S_B2]), sv), f[S_W2], __fmul_rn(om1, v.y));
-            own[c][k] = v;
-        }
-#pragma unroll
-        for (int k = 0; k < KP; ++k)
-            if (tid + k * NT < NS) L[c][cell[c][k]] = own[c][k];
         __syncthreads();
     };
-    for (int h = 0; h < nh; h += 2) {     // nh is even: red, then black
-        half(std::integral_constant<int, 0>{});
-        half(std::integral_constant<int, 1>{});
+    for (int h = nh; h > 0; h -= 2) {     // nh is even: red, then black
+        half(std::integral_constant<int, 0>{}, h - 1);
+        half(std::integral_constant<int, 1>{}, h - 2);
     }
     // the tile (distance >= S from the region's edge) is exact
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
+    for (int k = 0; k < KP; ++k) {
 #pragma unroll
-        for (int k = 0; k < KP; ++k) {
-            const int slot = tid + k * NT;
-            const int y = slot / RXh, s = slot % RXh;
-            const int x = 2 * s + par[c][k];
-            const int gx = X0 + x, gy = Y0 + y;
-            if (slot < NS && x >= S && x < S + TX && y >= S && y < S + TY && gx < W && gy < H) {
+        for (int p = 0; p < 2; ++p) {
+            const int x = 2 * s + p, y = y0 + k, gx = X0 + x, gy = Y0 + y;
+            if (act && x >= S && x < S + TX && y >= S && y < S + TY && gx < W && gy < H) {
                 const long long i = (long long)gy * W + gx;
-                du_out[i] = own[c][k].x;
-                dv_out[i] = own[c][k].y;
+                if (last) {
+                    const float2 u = field(A.u0, i);
+                    reinterpret_cast<Flow2*>(A.flow)[i] = {u.x + v[k][p].x, u.y + v[k][p].y};
+                } else {
+                    out[i] = v[k][p];
+                }
             }
         }
     }
 }
 
-__global__ __launch_bounds__(256) void k_var_out(VarArgs A, const float* __restrict__ du,
-                                                 const float* __restrict__ dv) {
+__global__ __launch_bounds__(256) void k_var_copy(VarArgs A) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= A.HW) return;
-    A.flow[2 * i] = A.u0[2 * i] + du[i];
-    A.flow[2 * i + 1] = A.u0[2 * i + 1] + dv[i];
+    A.flow[2 * i] = A.u0[2 * i] + 0.0f;
+    A.flow[2 * i + 1] = A.u0[2 * i + 1] + 0.0f;
 }
 
-__global__ __launch_bounds__(256) void k_var_zero(float* __restrict__ du, float* __restrict__ dv, long long n) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    du[i] = 0.0f;
-    dv[i] = 0.0f;
-}
-
-hipError_t launch_variational(const VarArgs& A, hipStream_t s) {
-    constexpr int TX = EPIC_VAR_TX, TY = EPIC_VAR_TY, S = EPIC_VAR_S, NT = EPIC_VAR_NT;
-    const dim3 g((unsigned)((A.HW + 255) / 256)), b(256);
-    const unsigned tiles = (unsigned)(((A.W + TX - 1) / TX) * ((A.H + TY - 1) / TY));
+template <class T>
+static void sweeps(const VarArgs& A, hipStream_t s) {
+    const dim3 g((unsigned)((A.HW + 255) / 256)), b(256), tiles((unsigned)T::tiles(A.H, A.W));
     int cur = 0;
-    hipLaunchKernelGGL(k_var_zero, g, b, 0, s, A.du[0], A.dv[0], A.HW);
-    hipLaunchKernelGGL(k_var_warp, g, b, 0, s, A);
-    hipLaunchKernelGGL(k_var_coef, g, b, 0, s, A);
     for (int f = 0; f < A.fixed_point; ++f) {
-        hipLaunchKernelGGL(k_var_weights, g, b, 0, s, A, A.du[cur], A.dv[cur]);
-        for (int h = 0; h < 2 * A.sor; h += S) {
-            const int nh = 2 * A.sor - h < S ? 2 * A.sor - h : S;
-            hipLaunchKernelGGL((k_var_sor<TX, TY, S, NT>), dim3(tiles), dim3(NT), 0, s, A, A.du[cur], A.dv[cur],
-                               A.du[cur ^ 1], A.dv[cur ^ 1], nh);
+        hipLaunchKernelGGL(k_var_weights, g, b, 0, s, A, A.d[cur]);
+        for (int h = 0; h < 2 * A.sor; h += T::S) {
+            const int nh = 2 * A.sor - h < T::S ? 2 * A.sor - h : T::S;
+            const int last = f + 1 == A.fixed_point && h + T::S >= 2 * A.sor;
+            hipLaunchKernelGGL(k_var_sor<T>, tiles, dim3(T::NT), 0, s, A, A.d[cur], A.d[cur ^ 1], nh,
+                               last);
             cur ^= 1;
         }
     }
-    hipLaunchKernelGGL(k_var_out, g, b, 0, s, A, A.du[cur], A.dv[cur]);
+}
+
+hipError_t launch_variational(const VarArgs& A, hipStream_t s) {
+    const dim3 g((unsigned)((A.HW + 255) / 256)), b(256);
+    if (A.fixed_point == 0 || A.sor == 0) {
+        hipLaunchKernelGGL(k_var_copy, g, b, 0, s, A);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_var_warp, g, b, 0, s, A);
+    hipLaunchKernelGGL(k_var_coef, g, b, 0, s, A);
+    // A launch takes as long as its busiest CU.  The wide tile where it leaves
+    // every CU at most one workgroup and the small one does not (1024 x 436: 359
+    // against 392 us); else the small tile: it fills more CUs of a small image
+    // (640 x 300: 278 against 334) and two of its workgroups share a CU of a
+    // large one (1280 x 720: 707 against 974).
+    if (VarWide::tiles(A.H, A.W) <= kVarCus && VarSmall::tiles(A.H, A.W) > kVarCus) sweeps<VarWide>(A, s);
+    else sweeps<VarSmall>(A, s);
     return hipGetLastError();
 }
 

@@ -1,0 +1,46 @@
+"""GPU: the refinement's two sweep tiles (32 x 32 and 64 x 28 pixels, 16
+half-sweeps a launch) at the sizes around their edges and at sweep counts
+that leave the last launch short, against the FP64 oracle.
+
+Tolerance.  An FP32 relaxation of the same system: at most 2 fixed-point
+steps of 9 sweeps, a tenth of the full iteration's 5 x 30, whose FP32 rounding
+moves a result by a mean of 8.3e-6 and at most 1.0e-3 px; the bars are those
+of the full iteration with their factor of ten, mean 1e-4 px, largest 1e-2 px.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+from scipy import ndimage
+
+from oracle import variational as va
+
+pytestmark = pytest.mark.gpu
+
+
+# 448 x 1023 and 421 x 1000 take the wide tile, the others the small one
+@pytest.mark.parametrize("H,W,ch,fixed_point,sor", [
+    (31, 33, 3, 2, 9), (32, 32, 1, 1, 8), (33, 65, 2, 2, 1), (64, 31, 4, 1, 9), (17, 48, 3, 2, 7),
+    (448, 1023, 1, 1, 9), (421, 1000, 3, 2, 7), (449, 1025, 1, 1, 9)])
+def test_refine_tile_edges(H, W, ch, fixed_point, sor):
+    import torch
+    import paper_1501_02565_amd as epic
+    rng = np.random.default_rng(H * 131 + W * 7 + ch)
+    I1 = np.stack([ndimage.gaussian_filter(rng.uniform(0, 1, (H, W)), 1.5) for _ in range(ch)], -1)
+    I2 = np.roll(I1, (1, 2), (0, 1)) + rng.uniform(0, 0.01, I1.shape)
+    u0 = np.stack([ndimage.gaussian_filter(rng.normal(0, 2, (H, W)), 4) + 2,
+                   ndimage.gaussian_filter(rng.normal(0, 2, (H, W)), 4) + 1], -1)
+    I1, I2, u0 = (np.ascontiguousarray(a, np.float32) for a in (I1, I2, u0))
+    print(f"[case] refine {H}x{W}x{ch} fixed_point={fixed_point} sor={sor}", flush=True)
+    # the field, aligned to a float only
+    f = torch.zeros(u0.size + 1, dtype=torch.float32, device="cuda")[1:].view(u0.shape)
+    f.copy_(torch.from_numpy(u0))
+    with epic.Context(workspace=256 << 20) as ctx:
+        got = ctx.refine(torch.from_numpy(I1).cuda(), torch.from_numpy(I2).cuda(), f, fixed_point=fixed_point, sor=sor)
+        torch.cuda.synchronize()
+        got = got.cpu().numpy()
+    d = np.sqrt(((got.astype(np.float64) - va.refine(I1, I2, u0, va.Params(fixed_point=fixed_point, sor=sor))) ** 2)
+                .sum(-1))
+    assert np.isfinite(got).all()
+    assert d.mean() <= 1e-4, d.mean()
+    assert d.max() <= 1e-2, d.max()
