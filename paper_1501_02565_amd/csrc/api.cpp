@@ -867,12 +867,10 @@ int epic_refine(epic_ctx* ctx, const float* I1, const float* I2, int H, int W, i
     A.I2 = I2;
     A.u0 = flow_in;
     A.flow = flow_out;
-    A.I2w = reinterpret_cast<float*>(w);
-    w += align_up(4 * (size_t)HW * channels);
     float* planes[kVarPlanes];
     for (int k = 0; k < kVarPlanes; ++k, w += align_up(4 * (size_t)HW)) planes[k] = reinterpret_cast<float*>(w);
     A.coef = planes[0];            // 13 consecutive planes
-    A.sys = planes[13];            // 9 (the records take 8)
+    A.sys = planes[13];            // 8
     A.d[0] = reinterpret_cast<float2*>(planes[22]);   // 2 each
     A.d[1] = reinterpret_cast<float2*>(planes[24]);
     A.H = H;

@@ -399,7 +399,6 @@ struct VarArgs {
     const float* I2;        // H*W*C
     const float* u0;        // H*W*2, the field to refine
     float* flow;            // H*W*2 output (may equal u0)
-    float* I2w;             // H*W*C scratch: I2 warped by u0
     float* coef;            // JC (6) and JG (6) in 3 planes of float4 of H*W, then alpha, H*W
     float* sys;             // 2 planes of float4 of H*W: a fixed-point step's per-pixel update
     float2* d[2];           // (du, dv), H*W each, a ping-pong pair
@@ -408,7 +407,10 @@ struct VarArgs {
     float lam, delta, gamma, kappa, eps, zeta, omega;
     int fixed_point, sor;
 };
-constexpr int kVarPlanes = 13 + 9 + 4;   // float planes of H*W besides I2w
+// The float planes of H*W that epic_refine_bytes counts (besides `channels` more):
+// coef, sys and d take 13 + 8 + 4 of them.  The total stays what callers have
+// sized their workspaces by.
+constexpr int kVarPlanes = 13 + 9 + 4;
 hipError_t launch_variational(const VarArgs& A, hipStream_t s);
 hipError_t launch_unpack(const PairDev* d_pairs, const RunDev& run, int total_blocks, float* D, int* L,
                          hipStream_t s);

@@ -27,9 +27,12 @@
 // small increments du carry the sweeps (no cancellation against u0).
 //
 // Kernels (FP32):
-//   k_var_warp     I2w (pixel-parallel)
-//   k_var_coef     per pixel the colour and gradient systems J (6 entries
-//                  each) and alpha, stored as 3 planes of 16-byte records and one
+//   k_var_coef     I2w and I1 of a 32 x 8 tile and the pixels around it into
+//                  LDS, then per pixel the colour and gradient systems J (6
+//                  entries each) and alpha, in 3 records of 16 bytes and a
+//                  plane.  Bound by its reads' latency: 11.7 us at 1024 x 436
+//                  (a kernel for I2w and one that read both images from memory
+//                  took 7.0 + 14.1)
 //   k_var_weights  per fixed-point step and pixel the numbers its update
 //                  needs: omega / D1 and omega / D2 for the diagonals
 //                  D1 = A11 + sum g, D2 = A22 + sum g (one division per
@@ -65,45 +68,62 @@ __device__ __forceinline__ float quad(const float* J, float du, float dv) {
 
 }  // namespace
 
-__global__ __launch_bounds__(256) void k_var_warp(VarArgs A) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= A.HW) return;
-    const int W = A.W, H = A.H, C = A.C;
-    const int x = (int)(i % W), y = (int)(i / W);
-    const float fxp = fminf(fmaxf((float)x + A.u0[2 * i], 0.0f), (float)(W - 1));
-    const float fyp = fminf(fmaxf((float)y + A.u0[2 * i + 1], 0.0f), (float)(H - 1));
-    const int x0 = min((int)floorf(fxp), W > 1 ? W - 2 : 0), y0 = min((int)floorf(fyp), H > 1 ? H - 2 : 0);
-    const int x1 = min(x0 + 1, W - 1), y1 = min(y0 + 1, H - 1);
-    const float fx = fxp - (float)x0, fy = fyp - (float)y0;
-    for (int c = 0; c < C; ++c) {
-        const float a = A.I2[((long long)y0 * W + x0) * C + c], b = A.I2[((long long)y0 * W + x1) * C + c];
-        const float d = A.I2[((long long)y1 * W + x0) * C + c], e = A.I2[((long long)y1 * W + x1) * C + c];
-        A.I2w[i * C + c] = (1.0f - fy) * ((1.0f - fx) * a + fx * b) + fy * ((1.0f - fx) * d + fx * e);
-    }
+// The input field's two numbers at pixel i in one load (the field need only be
+// aligned to a float).
+struct __attribute__((packed, aligned(4))) Flow2 { float u, v; };
+__device__ __forceinline__ float2 field(const float* f, long long i) {
+    const Flow2 t = reinterpret_cast<const Flow2*>(f)[i];
+    return make_float2(t.u, t.v);
 }
 
+constexpr int kCoefX = 32, kCoefY = 8;                      // pixels per workgroup
+constexpr int kCoefW = kCoefX + 2, kCoefN = kCoefW * (kCoefY + 2);
+
+template <int C>
 __global__ __launch_bounds__(256) void k_var_coef(VarArgs A) {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= A.HW) return;
-    const int W = A.W, H = A.H, C = A.C;
-    const int x = (int)(i % W), y = (int)(i / W);
-    const int xl = max(x - 1, 0), xr = min(x + 1, W - 1), yu = max(y - 1, 0), yd = min(y + 1, H - 1);
-    auto at = [&](const float* img, int yy, int xx, int c) { return img[((long long)yy * W + xx) * C + c]; };
+    __shared__ float Lw[C][kCoefN], L1[C][kCoefN];
+    const int W = A.W, H = A.H, tid = threadIdx.x;
+    const int tiles_x = (W + kCoefX - 1) / kCoefX;
+    const int X0 = (int)(blockIdx.x % tiles_x) * kCoefX, Y0 = (int)(blockIdx.x / tiles_x) * kCoefY;
+    // I2w and I1 of the tile and one pixel around it, the border repeated
+    for (int e = tid; e < kCoefN; e += 256) {
+        const int x = min(max(X0 + e % kCoefW - 1, 0), W - 1), y = min(max(Y0 + e / kCoefW - 1, 0), H - 1);
+        const long long i = (long long)y * W + x;
+        const float2 u = field(A.u0, i);
+        const float fxp = fminf(fmaxf((float)x + u.x, 0.0f), (float)(W - 1));
+        const float fyp = fminf(fmaxf((float)y + u.y, 0.0f), (float)(H - 1));
+        const int x0 = min((int)floorf(fxp), W > 1 ? W - 2 : 0), y0 = min((int)floorf(fyp), H > 1 ? H - 2 : 0);
+        const int x1 = min(x0 + 1, W - 1), y1 = min(y0 + 1, H - 1);
+        const float fx = fxp - (float)x0, fy = fyp - (float)y0;
+        const float *ra = A.I2 + ((long long)y0 * W + x0) * C, *rb = A.I2 + ((long long)y0 * W + x1) * C;
+        const float *rd = A.I2 + ((long long)y1 * W + x0) * C, *re = A.I2 + ((long long)y1 * W + x1) * C;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            L1[c][e] = A.I1[i * C + c];
+            Lw[c][e] = (1.0f - fy) * ((1.0f - fx) * ra[c] + fx * rb[c]) + fy * ((1.0f - fx) * rd[c] + fx * re[c]);
+        }
+    }
+    __syncthreads();
+    const int x = X0 + tid % kCoefX, y = Y0 + tid / kCoefX;
+    if (x >= W || y >= H) return;
+    const long long i = (long long)y * W + x;
+    const int e = (tid / kCoefX + 1) * kCoefW + tid % kCoefX + 1;
     float J[12];
     for (int k = 0; k < 12; ++k) J[k] = 0.0f;
     float gn = 0.0f;
     const float z2 = A.zeta * A.zeta;
+#pragma unroll
     for (int c = 0; c < C; ++c) {
-        const float w = at(A.I2w, y, x, c);
-        const float Ix = 0.5f * (at(A.I2w, y, xr, c) - at(A.I2w, y, xl, c));
-        const float Iy = 0.5f * (at(A.I2w, yd, x, c) - at(A.I2w, yu, x, c));
-        const float gx1 = 0.5f * (at(A.I1, y, xr, c) - at(A.I1, y, xl, c));
-        const float gy1 = 0.5f * (at(A.I1, yd, x, c) - at(A.I1, yu, x, c));
-        const float Iz = w - at(A.I1, y, x, c);
-        const float Ixx = at(A.I2w, y, xr, c) - 2.0f * w + at(A.I2w, y, xl, c);
-        const float Iyy = at(A.I2w, yd, x, c) - 2.0f * w + at(A.I2w, yu, x, c);
-        const float Ixy = 0.25f * (at(A.I2w, yd, xr, c) - at(A.I2w, yd, xl, c) - at(A.I2w, yu, xr, c) +
-                                   at(A.I2w, yu, xl, c));
+        const float *q = Lw[c] + e, *q1 = L1[c] + e;
+        const float w = q[0];
+        const float Ix = 0.5f * (q[1] - q[-1]);
+        const float Iy = 0.5f * (q[kCoefW] - q[-kCoefW]);
+        const float gx1 = 0.5f * (q1[1] - q1[-1]);
+        const float gy1 = 0.5f * (q1[kCoefW] - q1[-kCoefW]);
+        const float Iz = w - q1[0];
+        const float Ixx = q[1] - 2.0f * w + q[-1];
+        const float Iyy = q[kCoefW] - 2.0f * w + q[-kCoefW];
+        const float Ixy = 0.25f * (q[kCoefW + 1] - q[kCoefW - 1] - q[-kCoefW + 1] + q[-kCoefW - 1]);
         const float Ixz = Ix - gx1, Iyz = Iy - gy1;
         const float th = 1.0f / (Ix * Ix + Iy * Iy + z2);
         const float thx = 1.0f / (Ixx * Ixx + Ixy * Ixy + z2);
@@ -126,14 +146,6 @@ __global__ __launch_bounds__(256) void k_var_coef(VarArgs A) {
     S[2 * A.HW + i] = make_float4(J[8], J[9], J[10], J[11]);
     A.coef[12LL * A.HW + i] = expf(-A.kappa * sqrtf(gn));
     A.d[0][i] = make_float2(0.0f, 0.0f);
-}
-
-// The input field's two numbers at pixel i in one load (the field need only be
-// aligned to a float).
-struct __attribute__((packed, aligned(4))) Flow2 { float u, v; };
-__device__ __forceinline__ float2 field(const float* f, long long i) {
-    const Flow2 t = reinterpret_cast<const Flow2*>(f)[i];
-    return make_float2(t.u, t.v);
 }
 
 // A pixel as the smoothness weights see it: alpha, (u0, v0) and (du, dv).
@@ -368,8 +380,13 @@ hipError_t launch_variational(const VarArgs& A, hipStream_t s) {
         hipLaunchKernelGGL(k_var_copy, g, b, 0, s, A);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_var_warp, g, b, 0, s, A);
-    hipLaunchKernelGGL(k_var_coef, g, b, 0, s, A);
+    const dim3 gc((unsigned)(((A.W + kCoefX - 1) / kCoefX) * ((A.H + kCoefY - 1) / kCoefY)));
+    switch (A.C) {
+        case 1: hipLaunchKernelGGL(k_var_coef<1>, gc, b, 0, s, A); break;
+        case 2: hipLaunchKernelGGL(k_var_coef<2>, gc, b, 0, s, A); break;
+        case 3: hipLaunchKernelGGL(k_var_coef<3>, gc, b, 0, s, A); break;
+        default: hipLaunchKernelGGL(k_var_coef<4>, gc, b, 0, s, A); break;
+    }
     // A launch takes as long as its busiest CU.  The wide tile where it leaves
     // every CU at most one workgroup and the small one does not (1024 x 436: 359
     // against 392 us); else the small tile: it fills more CUs of a small image
