@@ -529,7 +529,7 @@ int run_pairs(epic_ctx* c, const epic_request* reqs, int n, hipStream_t stream, 
         // a pair whose cost map fails the check is not seeded (it then takes
         // the path of a pair without usable matches)
         if (e == hipSuccess && c->opt.debug_validate) e = launch_check_cost(dd, run, pix_blocks, stream);
-        if (e == hipSuccess) e = launch_seed(dd, run, seed_blocks, stream);
+        if (e == hipSuccess) e = launch_seed(dd, run, seed_blocks, nmax, stream);
         if (last) mark(1);
         if (dbg && dbg->stop_after == 1) break;
         const int pb0 = dbg && dbg->geo_passes > 0 ? dbg->geo_passes : budget(slot0);
@@ -543,7 +543,7 @@ int run_pairs(epic_ctx* c, const epic_request* reqs, int n, hipStream_t stream, 
             e = launch_check_transform(dd, run, pix_blocks, c->opt.debug_validate == 2, stream);
         if (e == hipSuccess) e = launch_graph_emit(dd, run, emit_blocks, total_px, stream);
         if (last) mark(3);
-        if (e == hipSuccess) e = launch_csr_scan(dd, run, stream);
+        if (e == hipSuccess) e = launch_csr_scan(dd, run, nmax, stream);
         if (last) mark(4);
         if (e == hipSuccess) e = launch_csr_scatter(dd, run, slot_blocks, stream);
         if (e == hipSuccess && c->opt.debug_validate) e = launch_check_graph(dd, run, slot_blocks, stream);

@@ -294,6 +294,7 @@ __device__ __forceinline__ int find_pair(int npairs, int idx, F base_of) {
 // ---------------------------------------------------------------------------
 // host-side launchers (one per stage; defined next to their kernels)
 // ---------------------------------------------------------------------------
+constexpr int kLargeN = 8192;       // matches of a pair above which seeding and the CSR scan take their large forms
 constexpr int PIX_BLOCK = 256;      // pixels per block of pixel-parallel kernels
 constexpr int ASSIGN_PPT = 4;      // pixels per thread of the assignment on calls with many pixels
 constexpr int EMIT_TW = 32, EMIT_TH = 16;  // pixel tile of one graph-emit block
@@ -303,14 +304,14 @@ constexpr int SLOT_BLOCK = 256;     // hash slots per block
 
 hipError_t launch_clear(const PairDev* d_pairs, const RunDev& run, int total_blocks, const PairDev* inline_host,
                         int n_inline, hipStream_t s);
-hipError_t launch_seed(const PairDev* d_pairs, const RunDev& run, int total_blocks, hipStream_t s);
+hipError_t launch_seed(const PairDev* d_pairs, const RunDev& run, int total_blocks, int nmax, hipStream_t s);
 hipError_t launch_check_cost(const PairDev* d_pairs, const RunDev& run, int total_blocks, hipStream_t s);
 hipError_t launch_geodesic(const PairDev* d_pairs, const RunDev& run, int tile_w, int tile_h, int threads,
                            int passes, hipStream_t s);
 hipError_t launch_geodesic64(const PairDev* d_pairs, const RunDev& run, int passes0, int passes1, hipStream_t s);
 hipError_t launch_graph_emit(const PairDev* d_pairs, const RunDev& run, int total_blocks, long long total_px,
                              hipStream_t s);
-hipError_t launch_csr_scan(const PairDev* d_pairs, const RunDev& run, hipStream_t s);
+hipError_t launch_csr_scan(const PairDev* d_pairs, const RunDev& run, int nmax, hipStream_t s);
 hipError_t launch_csr_scatter(const PairDev* d_pairs, const RunDev& run, int total_blocks, hipStream_t s);
 hipError_t launch_knn_fit(const PairDev* d_pairs, const RunDev& run, int total_blocks, int kmax, int nmax,
                           hipStream_t s);

@@ -187,61 +187,134 @@ __global__ __launch_bounds__(EMIT_NT / PPT) void k_graph_emit(const PairDev* __r
     }
 }
 
-// One workgroup of 1024 threads per pair.  Each thread sums a contiguous
-// chunk of degrees (a multiple of 4, read as uint4), the chunk sums are
-// scanned within each wavefront (DPP) and across the 16 wavefronts, and each
-// thread writes its chunk's row offsets.
+// One workgroup of 1024 threads per pair; the sums are scanned within each
+// wavefront (DPP) and across the wavefronts through LDS, and every thread
+// writes its row offsets.
+//
+// Up to 8192 matches each thread sums a contiguous chunk of degrees (a multiple
+// of 4, read as uint4): at most two loads per thread and one barrier (8000
+// matches 4.2 us, against 4.7 by segments; 300 matches 3.0 against 3.2).  A
+// longer chunk is a chain of loads, 40 bytes apart between threads (40000
+// matches: 19.2 us), so above that the degrees are taken in groups of SCAN_R
+// segments of 4096, consecutive threads reading consecutive uint4s and a
+// group's loads in flight together (8.8 us), bound by their latency.
+//
+// LARGE: the call has a pair above 8192 matches.  A kernel of its own: the
+// segments' registers and branches cost calls of small pairs 0.2 us.
+constexpr int SCAN_R = 4;
+
+template <bool LARGE>
 __global__ __launch_bounds__(1024) void k_csr_scan(const PairDev* __restrict__ pairs, RunDev run) {
     const PairDev& P = pairs[blockIdx.x];
-    __shared__ u32 s_wave[16];
+    __shared__ u32 s_wave[SCAN_R * 16];
     __shared__ int s_big[16];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int N = P.N;
-    const int chunk = ((N + 1023) / 1024 + 3) & ~3;
-    const int b = min(N, tid * chunk), e = min(N, b + chunk);
     const int visits = tid < kVisitWords ? *visit_word(P, tid) : 0;
-    u32 sum = 0, dor = 0;    // dor: OR of the degrees (FP32 records hold 16 bits)
-    if (e - b == chunk) {
-        for (int m = b; m < e; m += 4) {
-            const uint4 d = *reinterpret_cast<const uint4*>(P.deg + m);
-            sum += d.x + d.y + d.z + d.w;
-            dor |= d.x | d.y | d.z | d.w;
+    u32 dor = 0;             // OR of the degrees (FP32 records hold 16 bits)
+    u32 two_e_total = 0;     // the degrees of the groups before
+    static_assert(SCAN_R * 16 == 64, "a wavefront sum per lane");
+    for (u32 g0 = 0; LARGE && N > kLargeN;) {
+        const u32 left = (u32)N - g0;
+        uint4 d[SCAN_R];
+        u32 excl[SCAN_R];
+#pragma unroll
+        for (int r = 0; r < SCAN_R; ++r) {
+            const u32 m = g0 + r * 4096u + 4u * tid;
+            d[r] = make_uint4(0u, 0u, 0u, 0u);
+            if (m + 4u <= (u32)N) {
+                d[r] = *reinterpret_cast<const uint4*>(P.deg + m);
+            } else if (m < (u32)N) {
+                d[r].x = P.deg[m];
+                if (m + 1u < (u32)N) d[r].y = P.deg[m + 1u];
+                if (m + 2u < (u32)N) d[r].z = P.deg[m + 2u];
+            }
         }
-    } else {
-        for (int m = b; m < e; ++m) {
-            sum += P.deg[m];
-            dor |= P.deg[m];
+#pragma unroll
+        for (int r = 0; r < SCAN_R; ++r) {
+            u32 incl = 0;
+            excl[r] = 0;
+            if (r * 4096u < left) {       // one branch for the workgroup
+                const u32 sum = d[r].x + d[r].y + d[r].z + d[r].w;
+                dor |= d[r].x | d[r].y | d[r].z | d[r].w;
+                incl = (u32)wave::incl_scan((int)sum);
+                excl[r] = incl - sum;
+            }
+            if (lane == 63) s_wave[r * 16 + wid] = incl;
         }
+        const bool big = wave::ballot(dor > 0xffffu) != 0ull;
+        if (lane == 63) s_big[wid] = big ? 1 : 0;
+        __syncthreads();
+        const u32 ws = s_wave[lane];
+        const u32 incl = (u32)wave::incl_scan((int)ws);
+        const int before = (int)(two_e_total + incl - ws);
+#pragma unroll
+        for (int r = 0; r < SCAN_R; ++r) {
+            if (r * 4096u < left) {
+                const u32 m = g0 + r * 4096u + 4u * tid;
+                uint4 o;
+                o.x = (u32)__builtin_amdgcn_readlane(before, __builtin_amdgcn_readfirstlane(r * 16 + wid)) + excl[r];
+                o.y = o.x + d[r].x;
+                o.z = o.y + d[r].y;
+                o.w = o.z + d[r].z;
+                if (m + 4u <= (u32)N) {
+                    *reinterpret_cast<uint4*>(P.row_ptr + m) = o;
+                } else if (m < (u32)N) {
+                    P.row_ptr[m] = o.x;
+                    if (m + 1u < (u32)N) P.row_ptr[m + 1u] = o.y;
+                    if (m + 2u < (u32)N) P.row_ptr[m + 2u] = o.z;
+                }
+            }
+        }
+        two_e_total += (u32)__builtin_amdgcn_readlane((int)incl, 63);
+        if (left <= SCAN_R * 4096u) break;
+        g0 += SCAN_R * 4096u;
+        __syncthreads();     // s_wave is written again
     }
-    const u32 incl = (u32)wave::incl_scan((int)sum);
-    const bool big = wave::ballot(dor > 0xffffu) != 0ull;
-    if (lane == 63) {
-        s_wave[wid] = incl;
-        s_big[wid] = big ? 1 : 0;
-    }
-    __syncthreads();
-    u32 base = 0;
-    for (int w = 0; w < wid; ++w) base += s_wave[w];
-    u32 run_sum = base + incl - sum;
-    if (e - b == chunk) {
-        for (int m = b; m < e; m += 4) {
-            const uint4 d = *reinterpret_cast<const uint4*>(P.deg + m);
-            uint4 o;
-            o.x = run_sum;
-            o.y = o.x + d.x;
-            o.z = o.y + d.y;
-            o.w = o.z + d.z;
-            run_sum = o.w + d.w;
-            *reinterpret_cast<uint4*>(P.row_ptr + m) = o;
+    if (!LARGE || N <= kLargeN) {
+        const int chunk = ((N + 1023) / 1024 + 3) & ~3;
+        const int b = min(N, tid * chunk), e = min(N, b + chunk);
+        u32 sum = 0;
+        if (e - b == chunk) {
+            for (int m = b; m < e; m += 4) {
+                const uint4 d = *reinterpret_cast<const uint4*>(P.deg + m);
+                sum += d.x + d.y + d.z + d.w;
+                dor |= d.x | d.y | d.z | d.w;
+            }
+        } else {
+            for (int m = b; m < e; ++m) {
+                sum += P.deg[m];
+                dor |= P.deg[m];
+            }
         }
-    } else {
-        for (int m = b; m < e; ++m) {
-            P.row_ptr[m] = run_sum;
-            run_sum += P.deg[m];
+        const u32 incl = (u32)wave::incl_scan((int)sum);
+        const bool big = wave::ballot(dor > 0xffffu) != 0ull;
+        if (lane == 63) {
+            s_wave[wid] = incl;
+            s_big[wid] = big ? 1 : 0;
         }
+        __syncthreads();
+        u32 run_sum = incl - sum;
+        for (int w = 0; w < wid; ++w) run_sum += s_wave[w];
+        if (e - b == chunk) {
+            for (int m = b; m < e; m += 4) {
+                const uint4 d = *reinterpret_cast<const uint4*>(P.deg + m);
+                uint4 o;
+                o.x = run_sum;
+                o.y = o.x + d.x;
+                o.z = o.y + d.y;
+                o.w = o.z + d.z;
+                run_sum = o.w + d.w;
+                *reinterpret_cast<uint4*>(P.row_ptr + m) = o;
+            }
+        } else {
+            for (int m = b; m < e; ++m) {
+                P.row_ptr[m] = run_sum;
+                run_sum += P.deg[m];
+            }
+        }
+        for (int w = 0; w < 16; ++w) two_e_total += s_wave[w];
     }
-    u32 two_e_total = 0;
-    for (int w = 0; w < 16; ++w) two_e_total += s_wave[w];
     if (tid == 0) P.row_ptr[N] = two_e_total;
     if (tid < 64) {
         const int v = wave::sum(visits);
@@ -337,8 +410,9 @@ hipError_t launch_graph_emit(const PairDev* d_pairs, const RunDev& run, int tota
     return hipGetLastError();
 }
 
-hipError_t launch_csr_scan(const PairDev* d_pairs, const RunDev& run, hipStream_t s) {
-    hipLaunchKernelGGL(k_csr_scan, dim3(run.npairs), dim3(1024), 0, s, d_pairs, run);
+hipError_t launch_csr_scan(const PairDev* d_pairs, const RunDev& run, int nmax, hipStream_t s) {
+    if (nmax > kLargeN) hipLaunchKernelGGL(k_csr_scan<true>, dim3(run.npairs), dim3(1024), 0, s, d_pairs, run);
+    else hipLaunchKernelGGL(k_csr_scan<false>, dim3(run.npairs), dim3(1024), 0, s, d_pairs, run);
     return hipGetLastError();
 }
 

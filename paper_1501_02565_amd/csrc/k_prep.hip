@@ -79,7 +79,8 @@ __global__ __launch_bounds__(256) void k_clear(PairDev* __restrict__ pairs, RunD
     if (p == 0 && i0 < 3) run.wl_cnt[i0] = 0;
 }
 
-__global__ __launch_bounds__(256) void k_seed(const PairDev* __restrict__ pairs, RunDev run) {
+template <bool LARGE>
+__global__ __launch_bounds__(PIX_BLOCK) void k_seed(const PairDev* __restrict__ pairs, RunDev run) {
     const int p = find_pair(run.npairs, (int)blockIdx.x,
                             [&](int i) { return pairs[i].seed_block_base; });
     const PairDev& P = pairs[p];
@@ -108,13 +109,30 @@ __global__ __launch_bounds__(256) void k_seed(const PairDev* __restrict__ pairs,
         P.seed_pix[m] = pix;
     }
     // the usable matches are the lowest-indexed ones of the distinct seed
-    // pixels, counted by their first claims; one counter update per
-    // wavefront (updates of one address from every thread serialise)
-    const u64 nf = __builtin_amdgcn_ballot_w64(first);
-    const u64 no = __builtin_amdgcn_ballot_w64(m < P.N && pix < 0 && !rejected);
-    if ((threadIdx.x & 63) == 0) {
-        if (nf) atomicAdd(&P.counters[C_USED], (int)__popcll(nf));
-        if (no) atomicAdd(&P.counters[C_OUTSIDE], (int)__popcll(no));
+    // pixels, counted by their first claims.  Updates of one address serialise,
+    // about 12 ns each: one per wavefront, and above 8192 matches one per block
+    // (with 40000 matches the kernel took 10.3 us with one per wavefront, 5.3
+    // so; with 300 the block's sum costs 0.3 us more than it saves)
+    int nf = (int)__popcll(__builtin_amdgcn_ballot_w64(first));
+    int no = (int)__popcll(__builtin_amdgcn_ballot_w64(m < P.N && pix < 0 && !rejected));
+    int lead = threadIdx.x & 63;
+    if (LARGE && P.N > kLargeN) {
+        __shared__ int s_n[2][PIX_BLOCK / 64];
+        if (lead == 0) {
+            s_n[0][threadIdx.x >> 6] = nf;
+            s_n[1][threadIdx.x >> 6] = no;
+        }
+        __syncthreads();
+        nf = no = 0;
+        for (int w = 0; w < PIX_BLOCK / 64; ++w) {
+            nf += s_n[0][w];
+            no += s_n[1][w];
+        }
+        lead = threadIdx.x;
+    }
+    if (lead == 0) {
+        if (nf) atomicAdd(&P.counters[C_USED], nf);
+        if (no) atomicAdd(&P.counters[C_OUTSIDE], no);
     }
 }
 
@@ -149,8 +167,11 @@ hipError_t launch_clear(const PairDev* d_pairs, const RunDev& run, int total_blo
     return hipGetLastError();
 }
 
-hipError_t launch_seed(const PairDev* d_pairs, const RunDev& run, int total_blocks, hipStream_t s) {
-    hipLaunchKernelGGL(k_seed, dim3(total_blocks), dim3(PIX_BLOCK), 0, s, d_pairs, run);
+hipError_t launch_seed(const PairDev* d_pairs, const RunDev& run, int total_blocks, int nmax, hipStream_t s) {
+    if (nmax > kLargeN)
+        hipLaunchKernelGGL(k_seed<true>, dim3(total_blocks), dim3(PIX_BLOCK), 0, s, d_pairs, run);
+    else
+        hipLaunchKernelGGL(k_seed<false>, dim3(total_blocks), dim3(PIX_BLOCK), 0, s, d_pairs, run);
     return hipGetLastError();
 }
 
