@@ -324,11 +324,11 @@ def refine_leg(np, torch, epic, reps=10):
         r = va.refine(sc.image, sc.image2, u0)
         d = np.linalg.norm(g - r, axis=2)
         gt = sc.gt_flow.astype(np.float64)
-        sweep_launches = p.fixed_point * -(-2 * p.sor // 12)
+        sweep_launches = p.fixed_point * -(-2 * p.sor // 16)
         res = {"workload": sc.name + "_pair", "ms": round(ms, 4), "interp_plus_refine_ms": round(ms_both, 4),
                "mpix_s": round(HW / ms / 1e3, 2), "fixed_point": p.fixed_point, "sor": p.sor,
-               "launches": 4 + p.fixed_point + sweep_launches, "sweep_launches": sweep_launches,
-               "sweep_algorithmic_bytes_per_launch": 52.0 * HW,
+               "launches": 1 + p.fixed_point + sweep_launches, "sweep_launches": sweep_launches,
+               "sweep_algorithmic_bytes_per_launch": 48.0 * HW,
                "aee_vs_generating_motion": {"interpolated": float(np.linalg.norm(f0 - gt, axis=2).mean()),
                                             "refined": float(np.linalg.norm(f1 - gt, axis=2).mean())},
                "vs_oracle": {"mean_epe_px": float(d.mean()), "max_epe_px": float(d.max())}}
