@@ -741,6 +741,7 @@ int epic_interp_exact(epic_ctx* ctx, const float* cost, int H, int W, const floa
         A.ctl = reinterpret_cast<u32*>(take(4 * X_WORDS));
         A.pend[0] = reinterpret_cast<u32*>(take(4 * (size_t)N));
         A.pend[1] = reinterpret_cast<u32*>(take(4 * (size_t)N));
+        A.wide = reinterpret_cast<u32*>(take(4 * (size_t)N));
         A.big = reinterpret_cast<u32*>(take(4 * (size_t)N));
         A.bcount = reinterpret_cast<u32*>(take(4 * (size_t)nb));
         A.offset = reinterpret_cast<u32*>(take(4 * (size_t)nb));

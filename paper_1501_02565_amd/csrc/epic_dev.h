@@ -360,7 +360,8 @@ struct ExactArgs {
     float2* cu;             // H*W: cost and ubound
     u32* ctl;               // X_WORDS
     u32* pend[2];           // N each: sources put off, by round parity
-    u32* big;               // N: sources that outgrew LDS
+    u32* wide;              // N: sources that outgrew half a CU's LDS
+    u32* big;               // N: sources that outgrew all of it
     u32* bcount;            // entries of each 8 x 8 block
     u32* offset;            // their prefix sums
     uint4* meta;            // pool_cap: an entry's block, rank in it and source
@@ -376,9 +377,10 @@ enum : int {
     X_USED = 0,             // entries asked for
     X_LIMIT = 16,           // entries before this one are whole (the pool's end, or the
                             //   first that did not fit)
-    X_BIG = 32,             // sources that outgrew LDS
+    X_BIG = 32,             // sources that outgrew a CU's LDS
     X_PEND0 = 48,           // sources put off to an even round; odd: 16 words on
-    X_WORDS = 80
+    X_WIDE = 80,            // sources that outgrew half of it
+    X_WORDS = 96
 };
 // One workgroup per source (k_exact_reach.hip), in up to `rounds` rounds;
 // big_groups workgroups for the sources that outgrow LDS.

@@ -13,9 +13,10 @@
 // and the same bound cuts it off, so the distances are the same bits.
 //
 //   k_exact_reach    per source: the distances, stored as one entry of 64 per
-//                    reached block; k_exact_reach_big the same with the pages
-//                    in memory, for the sources that reach more blocks than
-//                    LDS holds.
+//                    reached block; k_exact_reach_wide the same with a whole
+//                    CU's LDS instead of half of it, for the sources that
+//                    reach more blocks, and k_exact_reach_big with the pages
+//                    in memory, for those that reach more still.
 //   k_exact_offsets  the entries of a block are counted as they are stored;
 //                    their prefix sums,
 //   k_exact_place    and each block's list of (entry, source).
@@ -28,10 +29,10 @@
 // the host launches as many rounds as could be needed at most (each source
 // reaching every block), and the unneeded ones leave at once.
 //
-// Measured on 1024 x 436, 8000 matches, K = 100: 5.7 ms for the whole call,
+// Measured on 1024 x 436, 8000 matches, K = 100: 5.3 ms for the whole call,
 // where the batched transforms and per-pixel heaps (k_exact.hip) took 28.4:
-// the distances 3.7 ms (bound by the latency of a page's LDS round trips and
-// of the costs it loads), the nearest and fits 1.7 ms (instruction issue).
+// the distances 3.5 ms (bound by the latency of a page's LDS round trips and
+// of the costs it loads), the nearest and fits 1.8 ms (instruction issue).
 #include <algorithm>
 
 #include "epic_dev.h"
@@ -46,15 +47,21 @@ constexpr u32 INF_BITS = 0x7f800000u;
 
 // Two workgroups fit a CU's LDS, with 1024 threads at 8 wavefronts per SIMD its
 // wave slots too.  512 and 768 threads took 6.9 and 6.1 ms where 1024 take
-// 5.7 (1024 x 436 below); 896, of which one workgroup fits, 7.9.
+// 5.7 (1024 x 436 below); 896, of which one workgroup fits, 7.9.  (These before
+// the wide form: the sources that outgrow this one took 0.74 ms with their pages
+// in memory, 0.35 with all of a CU's LDS; with a table of 40 blocks there too,
+// 0.35 and 0.54 in memory for those that reach further.)
+template <int PAGES_, int TB_>
 struct ReachCfg {
     static constexpr int NT = 1024, NW = NT / 64;       // threads, wavefronts
-    static constexpr int PAGES = 272;                  // pages; page 0 stays infinite
-    static constexpr int TB = 40;                      // blocks across the page table
+    static constexpr int PAGES = PAGES_;               // pages; page 0 stays infinite
+    static constexpr int TB = TB_;                     // blocks across the page table
 };
+using ReachMost = ReachCfg<272, 40>;
+using ReachWide = ReachCfg<544, 60>;     // a CU's LDS
 
+template <class C>
 struct ReachLds {
-    using C = ReachCfg;
     alignas(16) u32 page[C::PAGES][64];               // distance bits
     u32 tab[C::TB * C::TB];        // block -> page (0: none)
     u32 where[C::PAGES];           // page -> block (x | y << 16)
@@ -64,7 +71,8 @@ struct ReachLds {
     int npages, n[2], full;
     u32 base;
 };
-static_assert(2 * sizeof(ReachLds) <= 160 * 1024, "two workgroups per CU");
+static_assert(2 * sizeof(ReachLds<ReachMost>) <= 160 * 1024, "two workgroups per CU");
+static_assert(sizeof(ReachLds<ReachWide>) <= 160 * 1024, "one workgroup per CU");
 
 // Directions: (sx + 1) * 3 + (sy + 1), 4 is the block itself.
 template <int CONN>
@@ -174,19 +182,12 @@ __device__ __forceinline__ void seed_of(const ExactArgs& A, int s, int& sx, int&
 
 }  // namespace
 
-template <int CONN>
-__global__ __launch_bounds__(ReachCfg::NT) __attribute__((amdgpu_waves_per_eu(8))) void k_exact_reach(ExactArgs A) {
-    using C = ReachCfg;
+// One source's distances in LDS and their entries; false when it reaches more
+// blocks than there are pages, or further than the table.
+template <int CONN, class C>
+__device__ __forceinline__ bool reach_source(const ExactArgs& A, int s, ReachLds<C>& S) {
     constexpr int NT = C::NT, NW = C::NW, PAGES = C::PAGES, TB = C::TB;
-    __shared__ ReachLds S;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    int s = (int)blockIdx.x;
-    if (A.round > 0) {
-        const u32* const np = &A.ctl[X_PEND0 + 16 * (A.round & 1)];
-        if ((u32)s >= *np) return;
-        s = (int)A.pend[A.round & 1][s];
-    }
-    if (A.owner[s] == 0) return;
     int sx, sy;
     seed_of(A, s, sx, sy);
     const int BW = (A.W + 7) >> 3, BH = (A.H + 7) >> 3;
@@ -285,14 +286,38 @@ __global__ __launch_bounds__(ReachCfg::NT) __attribute__((amdgpu_waves_per_eu(8)
         __syncthreads();
         if (S.n[cur ^ 1] == 0) break;
     }
-    if (S.full) {
-        if (tid == 0) A.big[atomicAdd(&A.ctl[X_BIG], 1u)] = (u32)s;
-        return;
-    }
+    if (S.full) return false;
     const int m = S.npages - 1;
     store_entries<NT>(A, s, m, S.base,
                       [&](int i) { return (S.where[i + 1] >> 16) * (u32)BW + (S.where[i + 1] & 0xffffu); },
                       [&](int i, int l) { return S.page[i + 1][l]; });
+    return true;
+}
+
+template <int CONN>
+__global__ __launch_bounds__(ReachMost::NT) __attribute__((amdgpu_waves_per_eu(8))) void k_exact_reach(ExactArgs A) {
+    __shared__ ReachLds<ReachMost> S;
+    int s = (int)blockIdx.x;
+    if (A.round > 0) {
+        const u32* const np = &A.ctl[X_PEND0 + 16 * (A.round & 1)];
+        if ((u32)s >= *np) return;
+        s = (int)A.pend[A.round & 1][s];
+    }
+    if (A.owner[s] == 0) return;
+    if (!reach_source<CONN>(A, s, S) && threadIdx.x == 0) A.wide[atomicAdd(&A.ctl[X_WIDE], 1u)] = (u32)s;
+}
+
+// The sources that found no page left, with all of a CU's LDS; workgroup g
+// takes every gridDim.x-th of them.
+template <int CONN>
+__global__ __launch_bounds__(ReachWide::NT) void k_exact_reach_wide(ExactArgs A) {
+    __shared__ ReachLds<ReachWide> S;
+    const int count = (int)A.ctl[X_WIDE];
+    for (int w = (int)blockIdx.x; w < count; w += (int)gridDim.x) {
+        const int s = (int)A.wide[w];
+        if (!reach_source<CONN>(A, s, S) && threadIdx.x == 0) A.big[atomicAdd(&A.ctl[X_BIG], 1u)] = (u32)s;
+        __syncthreads();             // S is set up again
+    }
 }
 
 // The same with the pages in memory (block b's page at b, page `nblocks` all
@@ -562,6 +587,7 @@ __global__ __launch_bounds__(256) void k_exact_round(ExactArgs A) {
     if (i == 0) {
         A.ctl[X_USED] = 0u;
         A.ctl[X_LIMIT] = A.pool_cap;
+        A.ctl[X_WIDE] = 0u;
         A.ctl[X_BIG] = 0u;
         A.ctl[X_PEND0 + 16 * ((A.round & 1) ^ 1)] = 0u;
         if (A.round == 0) A.ctl[X_PEND0] = 0u;
@@ -575,10 +601,12 @@ hipError_t launch_exact_reach(const ExactArgs& A0, int conn, int rounds, int big
         A.round = r;
         hipLaunchKernelGGL(k_exact_round, dim3((unsigned)((NB + 255) / 256)), dim3(256), 0, s, A);
         if (conn == 4) {
-            hipLaunchKernelGGL(k_exact_reach<4>, dim3((unsigned)A.N), dim3(ReachCfg::NT), 0, s, A);
+            hipLaunchKernelGGL(k_exact_reach<4>, dim3((unsigned)A.N), dim3(ReachMost::NT), 0, s, A);
+            hipLaunchKernelGGL(k_exact_reach_wide<4>, dim3(256), dim3(ReachWide::NT), 0, s, A);
             hipLaunchKernelGGL(k_exact_reach_big<4>, dim3((unsigned)big_groups), dim3(512), 0, s, A);
         } else {
-            hipLaunchKernelGGL(k_exact_reach<8>, dim3((unsigned)A.N), dim3(ReachCfg::NT), 0, s, A);
+            hipLaunchKernelGGL(k_exact_reach<8>, dim3((unsigned)A.N), dim3(ReachMost::NT), 0, s, A);
+            hipLaunchKernelGGL(k_exact_reach_wide<8>, dim3(256), dim3(ReachWide::NT), 0, s, A);
             hipLaunchKernelGGL(k_exact_reach_big<8>, dim3((unsigned)big_groups), dim3(512), 0, s, A);
         }
         hipLaunchKernelGGL(k_exact_offsets, dim3(1), dim3(1024), 0, s, A);
