@@ -239,8 +239,10 @@ struct VarTile {
     static_assert(TY > 0 && NT <= 1024, "tile");
     static long long tiles(int H, int W) { return (long long)((W + TX - 1) / TX) * ((H + TY - 1) / TY); }
 };
-// 32 x 32 pixels, 1024 threads of 2 rows: two workgroups fit a CU.  64 x 28
+// 32 x 32 pixels, 1024 threads of 2 rows: two workgroups fit a CU.  32 x 16
+// pixels, 768 threads: less work per CU where there are CUs to spare.  64 x 28
 // pixels, 720 threads of 4 rows: one per CU, and a third less halo.
+using VarFine = VarTile<32, 16, 2, 24>;
 using VarSmall = VarTile<32, 16, 2, 32>;
 using VarWide = VarTile<64, 16, 4, 15>;
 constexpr int kVarCus = 256;
@@ -387,12 +389,14 @@ hipError_t launch_variational(const VarArgs& A, hipStream_t s) {
         case 3: hipLaunchKernelGGL(k_var_coef<3>, gc, b, 0, s, A); break;
         default: hipLaunchKernelGGL(k_var_coef<4>, gc, b, 0, s, A); break;
     }
-    // A launch takes as long as its busiest CU.  The wide tile where it leaves
-    // every CU at most one workgroup and the small one does not (1024 x 436: 359
-    // against 392 us); else the small tile: it fills more CUs of a small image
-    // (640 x 300: 278 against 334) and two of its workgroups share a CU of a
-    // large one (1280 x 720: 707 against 974).
-    if (VarWide::tiles(A.H, A.W) <= kVarCus && VarSmall::tiles(A.H, A.W) > kVarCus) sweeps<VarWide>(A, s);
+    // A launch takes as long as its busiest CU, so the smallest tile that leaves
+    // every CU at most one workgroup: the fine one (128 x 96: 188 us against 217
+    // with the small one, 400 x 300: 235 against 254), the small one (640 x 300:
+    // 278 against 334 with the wide one), the wide one (1024 x 436: 359 against
+    // 392 with the small one).  For larger images the small tile, of which two
+    // workgroups share a CU (1280 x 720: 707 against 974 with the wide one).
+    if (VarFine::tiles(A.H, A.W) <= kVarCus) sweeps<VarFine>(A, s);
+    else if (VarWide::tiles(A.H, A.W) <= kVarCus && VarSmall::tiles(A.H, A.W) > kVarCus) sweeps<VarWide>(A, s);
     else sweeps<VarSmall>(A, s);
     return hipGetLastError();
 }

@@ -1,5 +1,5 @@
-"""GPU: the refinement's two sweep tiles (32 x 32 and 64 x 28 pixels, 16
-half-sweeps a launch) at the sizes around their edges and at sweep counts
+"""GPU: the refinement's three sweep tiles (32 x 16, 32 x 32 and 64 x 28 pixels,
+16 half-sweeps a launch) at the sizes around their edges and at sweep counts
 that leave the last launch short, against the FP64 oracle.
 
 Tolerance.  An FP32 relaxation of the same system: at most 2 fixed-point
@@ -18,9 +18,11 @@ from oracle import variational as va
 pytestmark = pytest.mark.gpu
 
 
-# 448 x 1023 and 421 x 1000 take the wide tile, the others the small one
+# 448 x 1023 and 421 x 1000 take the wide tile, 353 x 481, 384 x 511 and
+# 449 x 1025 the small one, the others the fine one
 @pytest.mark.parametrize("H,W,ch,fixed_point,sor", [
     (31, 33, 3, 2, 9), (32, 32, 1, 1, 8), (33, 65, 2, 2, 1), (64, 31, 4, 1, 9), (17, 48, 3, 2, 7),
+    (15, 33, 1, 2, 9), (49, 64, 2, 2, 8), (256, 511, 1, 1, 9), (353, 481, 3, 2, 9), (384, 511, 1, 2, 8),
     (448, 1023, 1, 1, 9), (421, 1000, 3, 2, 7), (449, 1025, 1, 1, 9)])
 def test_refine_tile_edges(H, W, ch, fixed_point, sor):
     import torch
