@@ -301,11 +301,16 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
 
     int nvis = 1;               // entries in use (the same in every lane)
     int nsettled = 0;           // settled entries (the same in every lane)
-    // Lane state of group r, entry lane + 64 r: its distance as last read,
-    // infinity once it is settled (0 before), its edges in this step (0
-    // unless settled in it) and where they start among the step's edges.
-    // Kept as numbers, not as lane masks: the scalar unit, shared by the
-    // CU's four SIMDs, is nearly as busy with this kernel as the SIMDs are.
+    // Lane state of group r, entry lane + 64 r: its distance as last read, a
+    // mark once it is settled (0 before), its edges in this step (0 unless
+    // settled in it) and where they start among the step's edges.  Kept as
+    // numbers, not as lane masks: the scalar unit, shared by the CU's four
+    // SIMDs, is nearly as busy with this kernel as the SIMDs are.  The mark is
+    // all ones in FP32, above an infinity's bits: costs may be any finite
+    // numbers, so dmin plus a lightest edge can be infinite, and an entry must
+    // not be settled twice.  Sums of FP64 (of at most FLT_MAX a pixel) stay
+    // finite; their mark is infinity.
+    const RT SETTLED = F64 ? RINF : (RT)__uint_as_float(~0u);
     RT d[R], sf[R];
     u32 dg[R], off[R];
 #pragma unroll
@@ -322,7 +327,7 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
     // or -1 when the search is done.
     auto step = [&](auto ru_c, int ru) -> int {
         constexpr int RU = decltype(ru_c)::value;
-        RT mi[R], x[R];          // x: the distance on the frontier, infinite elsewhere
+        RT mi[R], x[R];          // x: the distance on the frontier, the mark of settled entries
         RT fmin = RINF;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -363,10 +368,12 @@ __device__ __forceinline__ bool knn_fit_one(const PairDev& P, const RunDev& run,
         for (int r = 0; r < R; ++r) {
             newly[r] = false;
             if (RU ? r >= RU : r >= ru) continue;
-            const u64 m = wave::ballot(x[r] <= dmin + mi[r]);
+            u64 m;
+            if constexpr (F64) m = wave::ballot(x[r] <= dmin + mi[r]);
+            else m = wave::ballot(__float_as_uint(x[r]) <= __float_as_uint(dmin + mi[r]));     // (in the bits' order)
             newly[r] = __builtin_amdgcn_inverse_ballot_w64(m);
             nsettled += __popcll(m);
-            sf[r] = newly[r] ? RINF : sf[r];
+            sf[r] = newly[r] ? SETTLED : sf[r];
             dg[r] = newly[r] ? dg[r] : 0u;
             my_edges += dg[r];
         }
