@@ -297,19 +297,37 @@ int epic_interp_image(epic_ctx* ctx, const float* image, int H, int W, int chann
  * exp(-a D_G), and its own NW (Eq. 1) or LA (Eq. 2) estimate evaluated at
  * p.  The approximated interpolation runs first: its distances (each the
  * length of a path of the pixel graph) bound, at every pixel, the distance
- * of the K-th nearest match; then one single-source transform per match (in
- * chunks of up to 1024 that fit the workspace) keeps only distances within
- * those bounds, a per-pixel selection folds each chunk into the pixels' K
- * nearest, and a per-pixel fit ends it; the near-collinear LA rule and FP64
- * routing are those of epic_interp.  The bound only skips work: the result
- * is the same as with full-image transforms.
+ * of the K-th nearest match.  Then one of two forms, with the same result
+ * bit for bit:
+ *   per match  one workgroup per match computes its distances within those
+ *              bounds and stores them by blocks of 8 x 8 pixels; a wavefront
+ *              per pixel sorts out its K nearest and fits them;
+ *   batched    single-source transforms of the whole image, a match each,
+ *              in chunks of up to 1024 that fit the workspace; a per-pixel
+ *              selection folds each chunk into the pixels' K nearest, and a
+ *              per-pixel fit ends it.
+ * The near-collinear LA rule and FP64 routing are those of epic_interp.  The
+ * bound only skips work: the result is the same as with full-image
+ * transforms.
+ * With B = ceil(W/8) * ceil(H/8) blocks and R = B * min(1, 2 K / N) of them
+ * reached by a match, the per-match form is taken where it is the faster
+ * one and has the room:
+ *   - N >= min(R, 768), or min(B, 2 R) <= 256 (R <= 128 when N < 16);
+ *   - the workspace leaves (beside the bytes below and the 8*H*W + 16*N +
+ *     8*B of the form's own arrays) room for B * (N / 8 + 2) entries of 280
+ *     bytes in three quarters of the rest; with R > 352, for 2 * N * R
+ *     entries and, in the other quarter, 256 times 276 * B bytes;
+ *   - no prune_px, no debug_validate, N * B < 2^31.
+ * (1024 x 436 with 8000 matches and K = 100: from 2.9 GB on.)  Other calls
+ * take the batched form.
  * Arguments as in epic_interp, with K <= 128 and a context created with
  * precision 0 (EPIC_ERR_ARG otherwise).  The workspace must hold
  * 8*K*H*W + 4*H*W + N + 8*N*K bytes plus 34 KB at its end for the
  * pixels' lists, the bounds, the approximated lists, the boxes of tiles a
  * chunk's transforms reached and alignment, besides
- * epic_workspace_bytes(H, W, N, K, mode, 0) for the approximated pass and,
- * per match of a chunk, epic_workspace_bytes(H, W, 1, 1, mode, 0)
+ * epic_workspace_bytes(H, W, N, K, mode, 0) for the approximated pass or,
+ * where that is more, for the batched form epic_workspace_bytes(H, W, 1, 1,
+ * mode, 0) per match of a chunk
  * (EPIC_ERR_WORKSPACE when not even one fits); a chunk of 1024 at
  * 1024 x 436 needs about 3.7 GB.  No per-call statistics (epic_get_stats
  * refers to no pair afterwards).  Asynchronous on `stream`. */

@@ -16,6 +16,7 @@
 
 #include "epic.h"
 #include "epic_dev.h"
+#include "exact_plan.h"
 
 using namespace epic;
 
@@ -26,17 +27,13 @@ constexpr int kAutoPassesStart = 16;    // automatic budget before any call fini
 constexpr int kAutoPassesHistory = 8;   // recent needs the automatic budget covers
 constexpr int kAutoPassesMin = 4;
 constexpr int kRing = 4;             // descriptor upload slots
-constexpr size_t kAlign = 256;
 constexpr int kMaxK = 256;
-constexpr int kExactRounds = 8;      // rounds of the exact interpolation's per-match path, at most
 constexpr int kStages = 8;
 constexpr int kProfRing = 64;
 const char* const kStageNames[kStages] = {"clear", "seed", "geodesic", "graph_emit",
                                           "csr_scan", "csr_scatter", "knn_fit", "assign"};
 
 thread_local std::string g_last_error;
-
-size_t align_up(size_t v) { return (v + kAlign - 1) & ~(kAlign - 1); }
 
 int next_pow2(long long v) {
     int p = 1;
@@ -720,59 +717,38 @@ int epic_interp_exact(epic_ctx* ctx, const float* cost, int H, int W, const floa
     epic_request full{cost, H, W, matches, N, K, a, mode, flow};
     int rc = run_pairs(ctx, &full, 1, st, &approx, nullptr, tail);
     if (rc != EPIC_OK) return rc;
-    // with room for them, the distances take one workgroup per match and lie
-    // in a pool of entries (64 distances of one match in one 8 x 8 block); the
-    // pool is filled again in further rounds when it could overflow, as many
-    // as the worst case (each match reaching every block) needs.  The smaller
-    // workspaces, the calls whose matches the consistency check has
-    // renumbered, and the self-checks take the batched transforms below.
-    int rounds = 0, big_groups = 0;
-    {
-        const long long bw = (W + 7) / 8, bh = (H + 7) / 8, nb = bw * bh;
-        char* cur = ctx->ws + kFixed;
-        char* const end = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(tail_p) - align_up(8 * (size_t)HW)) &
-                                                  ~(uintptr_t)(kAlign - 1));
-        auto take = [&](size_t bytes) {
-            char* q = cur;
-            cur += align_up(bytes);
-            return q;
-        };
-        A.cu = reinterpret_cast<float2*>(end);
-        A.ctl = reinterpret_cast<u32*>(take(4 * X_WORDS));
-        A.pend[0] = reinterpret_cast<u32*>(take(4 * (size_t)N));
-        A.pend[1] = reinterpret_cast<u32*>(take(4 * (size_t)N));
-        A.wide = reinterpret_cast<u32*>(take(4 * (size_t)N));
-        A.big = reinterpret_cast<u32*>(take(4 * (size_t)N));
-        A.bcount = reinterpret_cast<u32*>(take(4 * (size_t)nb));
-        A.offset = reinterpret_cast<u32*>(take(4 * (size_t)nb));
-        A.scratch_words = (size_t)(nb + 1) * 64 + 5 * (size_t)nb;
-        const size_t group_b = align_up(4 * A.scratch_words);
-        A.scratch_words = group_b / 4;
-        const size_t left = end > cur ? (size_t)(end - cur) : 0;
-        big_groups = (int)std::min<size_t>(256, left / 4 / group_b);
-        // 16 + 8 + 256 bytes an entry, and the arrays' alignment
-        const size_t entries_b = left - (size_t)big_groups * group_b;
-        const long long cap = entries_b > 3 * kAlign ? (long long)((entries_b - 3 * kAlign) / 280) : 0;
-        const long long per_round = cap / nb - 1;           // sources a round places at least
-        if (big_groups >= 1 && per_round >= 1 && cap < (1LL << 31) && (long long)N * nb < (1LL << 31) && bw < 65536 &&
-            bh < 65536 && end >= ctx->ws + ctx->last_used && !(ctx->opt.prune_px > 0.0f) && !ctx->opt.debug_validate) {
-            const long long r = (N + per_round - 1) / per_round;
-            if (r <= kExactRounds) rounds = (int)r;
-        }
-        if (rounds > 0) {
-            A.scratch = reinterpret_cast<u32*>(take((size_t)big_groups * group_b));
-            A.pool_cap = (u32)cap;
-            A.meta = reinterpret_cast<uint4*>(take(16 * (size_t)cap));
-            A.order = reinterpret_cast<uint2*>(take(8 * (size_t)cap));
-            A.pool = reinterpret_cast<u32*>(take(256 * (size_t)cap));
-        } else {
-            A.cu = nullptr;
-        }
+    // where it is the faster form and has the room (exact_plan.h), the
+    // distances take one workgroup per match and lie in a pool of entries (64
+    // distances of one match in one 8 x 8 block), filled again in further
+    // rounds when it could overflow.  Other calls, those whose matches the
+    // consistency check has renumbered, and the self-checks take the batched
+    // transforms below.
+    static_assert(X_WORDS == kExactCtl, "the control words");
+    ExactPlan plan;
+    if (!(ctx->opt.prune_px > 0.0f) && !ctx->opt.debug_validate)
+        plan = exact_plan(H, W, N, K, kFixed, ctx->last_used, (size_t)(tail_p - ctx->ws));
+    if (plan.rounds > 0) {
+        auto at = [&](size_t offset) { return reinterpret_cast<u32*>(ctx->ws + offset); };
+        A.cu = reinterpret_cast<float2*>(ctx->ws + plan.cu);
+        A.ctl = at(plan.ctl);
+        A.pend[0] = at(plan.pend[0]);
+        A.pend[1] = at(plan.pend[1]);
+        A.wide = at(plan.wide);
+        A.big = at(plan.big);
+        A.bcount = at(plan.bcount);
+        A.offset = at(plan.offset);
+        A.scratch = at(plan.scratch);
+        A.scratch_words = plan.scratch_words;
+        A.meta = reinterpret_cast<uint4*>(ctx->ws + plan.meta);
+        A.order = reinterpret_cast<uint2*>(ctx->ws + plan.order);
+        A.pool = at(plan.pool);
+        A.pool_cap = plan.pool_cap;
     }
     if (launch_exact_owner(ctx->last_desc, A, st) != hipSuccess) return EPIC_ERR_HIP;
     if (launch_exact_bound(ctx->last_desc, A, st) != hipSuccess) return EPIC_ERR_HIP;
-    if (rounds > 0) {
-        if (launch_exact_reach(A, ctx->opt.connectivity, rounds, big_groups, st) != hipSuccess) return EPIC_ERR_HIP;
+    if (plan.rounds > 0) {
+        if (launch_exact_reach(A, ctx->opt.connectivity, plan.rounds, plan.big_groups, st) != hipSuccess)
+            return EPIC_ERR_HIP;
         ctx->last_npairs = 0;          // no per-call statistics
         return EPIC_OK;
     }
