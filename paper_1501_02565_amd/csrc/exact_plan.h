@@ -83,6 +83,10 @@ inline ExactPlan exact_plan(int H, int W, int N, int K, size_t begin, size_t use
     const long long cap = entries_b > 3 * kAlign ? (long long)((entries_b - 3 * kAlign) / 280) : 0;
     const long long per_round = cap / nb - 1;               // matches a round places at least
     if (p.big_groups < 1 || per_round < 1 || end < used) return batched;
+    // a launch has fewer than 2^32 threads: 1024 a match, 64 a pixel of the
+    // blocks (the batched form takes matches in chunks, and 64 a pixel of the
+    // image)
+    if (N >= 1 << 22 || nb >= 1 << 20) return batched;
     // 32-bit entries, 16-bit block coordinates
     if (cap >= (1LL << 31) || (long long)N * nb >= (1LL << 31) || bw >= 65536 || bh >= 65536) return batched;
     const long long rounds = (N + per_round - 1) / per_round;

@@ -69,6 +69,18 @@ def test_form_by_room(size, part, form):
     assert ("per match" if p["rounds"] else "batched") == form
 
 
+@pytest.mark.parametrize("size,form", [
+    ((16, 16, (1 << 22) - 1, 4), "per match"), ((16, 16, 1 << 22, 4), "batched"),
+    ((8192, 8184, 2000, 1), "per match"), ((8191, 8192, 1100, 1), "batched"),      # 1024 * 1023 and 2^20 blocks
+])
+def test_launches_below_2_32_threads(size, form):
+    H, W, N, K = size
+    p = plan(8 << 30, H, W, N, K) if H < 100 else plan_at(H, W, N, K, 1 << 20, 1 << 20, 400 << 30)
+    nb = -(-H // 8) * -(-W // 8)
+    assert ("per match" if p["rounds"] else "batched") == form
+    assert p["rounds"] == 0 or max(1024 * N, 64 * 64 * nb) < 1 << 32
+
+
 def test_layout():
     """Arrays of the per-match form: in order, apart, within the space the
     approximated pass and the lists leave them; every match placed in the

@@ -49,6 +49,29 @@ CASES = [
 ]
 
 
+def test_four_million_matches():
+    """Above the per-match form's launch (1024 threads a match): nearly all of
+    the matches fall on pixels that a lower index holds."""
+    import torch
+    import paper_1501_02565_amd as epic
+    H = W = 16
+    N, K = 1 << 22, 4
+    sc = random_case(H, W, 120, seed=92, K=K)
+    assert sc.N == 120
+    m = torch.from_numpy(sc.matches).cuda()
+    many = m.repeat(-(-N // 120), 1)[:N].contiguous()
+    many[120:, 2:] += 5.0
+    cost = torch.from_numpy(sc.cost).cuda()
+    ws = lists_bytes(H, W, N, K) + epic.workspace_bytes(H, W, N, K) + (2 << 30)
+    assert plan(ws, H, W, N - 1, K)["rounds"] >= 1 and plan(ws, H, W, N, K)["rounds"] == 0
+    print(f"[case] exact 16x16, {N} matches", flush=True)
+    with epic.Context(0, 64 << 20) as c:
+        ref = c.interp_exact(cost, m, K, 1.0, 1)
+    with epic.Context(0, ws) as c:
+        got = c.interp_exact(cost, many, K, 1.0, 1)
+    assert torch.equal(got, ref)
+
+
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_forms_agree(case):
     import torch
