@@ -79,12 +79,13 @@ __device__ __forceinline__ float2 field(const float* f, long long i) {
 constexpr int kCoefX = 32, kCoefY = 8;                      // pixels per workgroup
 constexpr int kCoefW = kCoefX + 2, kCoefN = kCoefW * (kCoefY + 2);
 
-template <int C>
-__global__ __launch_bounds__(256) void k_var_coef(VarArgs A) {
+template <int C, bool SLICED>
+__global__ __launch_bounds__(256) void k_var_coef(VarArgs A, unsigned tile0) {
     __shared__ float Lw[C][kCoefN], L1[C][kCoefN];
     const int W = A.W, H = A.H, tid = threadIdx.x;
     const int tiles_x = (W + kCoefX - 1) / kCoefX;
-    const int X0 = (int)(blockIdx.x % tiles_x) * kCoefX, Y0 = (int)(blockIdx.x / tiles_x) * kCoefY;
+    const unsigned tile = SLICED ? tile0 + blockIdx.x : blockIdx.x;
+    const int X0 = (int)(tile % tiles_x) * kCoefX, Y0 = (int)(tile / tiles_x) * kCoefY;
     // I2w and I1 of the tile and one pixel around it, the border repeated
     for (int e = tid; e < kCoefN; e += 256) {
         const int x = min(max(X0 + e % kCoefW - 1, 0), W - 1), y = min(max(Y0 + e / kCoefW - 1, 0), H - 1);
@@ -247,16 +248,17 @@ using VarSmall = VarTile<32, 16, 2, 32>;
 using VarWide = VarTile<64, 16, 4, 15>;
 constexpr int kVarCus = 256;
 
-template <class T>
+template <class T, bool SLICED>
 __global__ __launch_bounds__(T::NT) void k_var_sor(VarArgs A, const float2* __restrict__ in, float2* __restrict__ out,
-                                                   int nh, int last) {
+                                                   int nh, int last, unsigned tile0) {
     constexpr int TX = T::TX, S = T::S, KP = T::KP, NR = T::NR, RY = T::RY, TY = T::TY, RXh = T::RXh, NT = T::NT;
     constexpr int LW = RXh + 2, LN = (RY + 2) * LW;
     __shared__ float2 L[2][LN];
     const int tid = threadIdx.x;
     const int W = A.W, H = A.H;
     const int tiles_x = (W + TX - 1) / TX;
-    const int X0 = (int)(blockIdx.x % tiles_x) * TX - S, Y0 = (int)(blockIdx.x / tiles_x) * TY - S;
+    const unsigned tile = SLICED ? tile0 + blockIdx.x : blockIdx.x;
+    const int X0 = (int)(tile % tiles_x) * TX - S, Y0 = (int)(tile / tiles_x) * TY - S;
     // the pads around the region: read by its outermost ring only
     for (int k = tid; k < 2 * (2 * LW + 2 * RY); k += NT) {
         const int a = k & 1, q = k >> 1;
@@ -360,17 +362,35 @@ __global__ __launch_bounds__(256) void k_var_copy(VarArgs A) {
     A.flow[2 * i + 1] = A.u0[2 * i + 1] + 0.0f;
 }
 
+// One launch, or (SLICED kernels, told the first tile) several of at most 2^21
+// tiles: a launch has fewer than 2^32 threads, which very narrow images would
+// pass (a tile is 32 pixels wide at least: 1 pixel by 2^27 is 2^22 tiles of
+// 1024 threads).  Kernels of their own: reading the first tile costs a sweep
+// launch 0.08 us.
+template <class F>
+static void in_slices(long long tiles, F launch) {
+    constexpr long long SLICE = 1 << 21;
+    if (tiles <= SLICE) {
+        launch(std::false_type{}, dim3((unsigned)tiles), 0u);
+        return;
+    }
+    for (long long t = 0; t < tiles; t += SLICE)
+        launch(std::true_type{}, dim3((unsigned)(tiles - t < SLICE ? tiles - t : SLICE)), (unsigned)t);
+}
+
 template <class T>
 static void sweeps(const VarArgs& A, hipStream_t s) {
-    const dim3 g((unsigned)((A.HW + 255) / 256)), b(256), tiles((unsigned)T::tiles(A.H, A.W));
+    const dim3 g((unsigned)((A.HW + 255) / 256)), b(256);
     int cur = 0;
     for (int f = 0; f < A.fixed_point; ++f) {
         hipLaunchKernelGGL(k_var_weights, g, b, 0, s, A, A.d[cur]);
         for (int h = 0; h < 2 * A.sor; h += T::S) {
             const int nh = 2 * A.sor - h < T::S ? 2 * A.sor - h : T::S;
             const int last = f + 1 == A.fixed_point && h + T::S >= 2 * A.sor;
-            hipLaunchKernelGGL(k_var_sor<T>, tiles, dim3(T::NT), 0, s, A, A.d[cur], A.d[cur ^ 1], nh,
-                               last);
+            in_slices(T::tiles(A.H, A.W), [&](auto sliced, dim3 tiles, unsigned tile0) {
+                hipLaunchKernelGGL((k_var_sor<T, decltype(sliced)::value>), tiles, dim3(T::NT), 0, s, A, A.d[cur],
+                                   A.d[cur ^ 1], nh, last, tile0);
+            });
             cur ^= 1;
         }
     }
@@ -382,13 +402,16 @@ hipError_t launch_variational(const VarArgs& A, hipStream_t s) {
         hipLaunchKernelGGL(k_var_copy, g, b, 0, s, A);
         return hipGetLastError();
     }
-    const dim3 gc((unsigned)(((A.W + kCoefX - 1) / kCoefX) * ((A.H + kCoefY - 1) / kCoefY)));
-    switch (A.C) {
-        case 1: hipLaunchKernelGGL(k_var_coef<1>, gc, b, 0, s, A); break;
-        case 2: hipLaunchKernelGGL(k_var_coef<2>, gc, b, 0, s, A); break;
-        case 3: hipLaunchKernelGGL(k_var_coef<3>, gc, b, 0, s, A); break;
-        default: hipLaunchKernelGGL(k_var_coef<4>, gc, b, 0, s, A); break;
-    }
+    const long long coef_tiles = (long long)((A.W + kCoefX - 1) / kCoefX) * ((A.H + kCoefY - 1) / kCoefY);
+    in_slices(coef_tiles, [&](auto sliced, dim3 tiles, unsigned tile0) {
+        constexpr bool S = decltype(sliced)::value;
+        switch (A.C) {
+            case 1: hipLaunchKernelGGL((k_var_coef<1, S>), tiles, b, 0, s, A, tile0); break;
+            case 2: hipLaunchKernelGGL((k_var_coef<2, S>), tiles, b, 0, s, A, tile0); break;
+            case 3: hipLaunchKernelGGL((k_var_coef<3, S>), tiles, b, 0, s, A, tile0); break;
+            default: hipLaunchKernelGGL((k_var_coef<4, S>), tiles, b, 0, s, A, tile0); break;
+        }
+    });
     // A launch takes as long as its busiest CU, so the smallest tile that leaves
     // every CU at most one workgroup: the fine one (128 x 96: 188 us against 217
     // with the small one, 400 x 300: 235 against 254), the small one (640 x 300:
