@@ -207,8 +207,10 @@ class Context:
         """The exact per-pixel geodesic interpolation (Table 2, "Geodesic
         (exact)"): each pixel's own K nearest matches under the geodesic
         distance and its own fit.  Needs a workspace of about
-        8*K*H*W + N + 512 bytes plus, per match processed at once,
-        workspace_bytes(H, W, 1, 1)."""
+        8*K*(H*W + N) + 4*H*W + N + 34 KB plus workspace_bytes(H, W, N, K)
+        or, where that is more, workspace_bytes(H, W, 1, 1) per match
+        processed at once; with more room the faster form that include/epic.h
+        describes is taken where it is the faster one."""
         torch = _torch()
         _check_tensor(cost, "cost", torch.float32)
         _check_tensor(matches, "matches", torch.float32, (4,))

@@ -18,8 +18,9 @@
 // matches that hold their pixel (placed, lowest index), so dropped and
 // duplicate matches never enter a list.  k_exact_fit then fits each pixel
 // (fit.h) with the pixel as the anchor.
-// This form serves small workspaces; given room, k_exact_reach.hip takes the
-// steps after the bounds.
+// This form serves small workspaces and matches that reach far (N a few times
+// K); otherwise k_exact_reach.hip takes the steps after the bounds (the choice:
+// exact_plan.h).
 #include "epic_dev.h"
 #include "fit.h"
 #include "wave.h"

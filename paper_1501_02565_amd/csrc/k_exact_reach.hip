@@ -31,8 +31,10 @@
 //
 // Measured on 1024 x 436, 8000 matches, K = 100: 5.3 ms for the whole call,
 // where the batched transforms and per-pixel heaps (k_exact.hip) took 28.4:
-// the distances 3.5 ms (bound by the latency of a page's LDS round trips and
-// of the costs it loads), the nearest and fits 1.8 ms (instruction issue).
+// the distances 3.4 ms (bound by the latency of a page's LDS round trips and
+// of the costs it loads), the nearest and fits 1.9 ms (instruction issue).
+// Where most matches reach more blocks than LDS holds, the batched form is the
+// faster one: exact_plan.h chooses.
 #include <algorithm>
 
 #include "epic_dev.h"
@@ -47,10 +49,12 @@ constexpr u32 INF_BITS = 0x7f800000u;
 
 // Two workgroups fit a CU's LDS, with 1024 threads at 8 wavefronts per SIMD its
 // wave slots too.  512 and 768 threads took 6.9 and 6.1 ms where 1024 take
-// 5.7 (1024 x 436 below); 896, of which one workgroup fits, 7.9.  (These before
-// the wide form: the sources that outgrow this one took 0.74 ms with their pages
-// in memory, 0.35 with all of a CU's LDS; with a table of 40 blocks there too,
-// 0.35 and 0.54 in memory for those that reach further.)
+// 5.7 (1024 x 436, 8000 matches, K = 100); 896, of which one workgroup fits, 7.9.
+// (These before the wide form: there the sources that outgrow this one took 0.74
+// ms with their pages in memory, 0.35 with all of a CU's LDS; with a table of 40
+// blocks there too, 0.35 and 0.54 in memory for those that reach further.  How
+// many outgrow it is the scene's: another one of these sizes has wide sources
+// of 0.93 ms.)
 template <int PAGES_, int TB_>
 struct ReachCfg {
     static constexpr int NT = 1024, NW = NT / 64;       // threads, wavefronts

@@ -68,10 +68,11 @@ __device__ __forceinline__ void lds_order() { __asm__ __volatile__("" ::: "memor
 // their entry with that one read; probing slot by slot with a
 // compare-and-swap each cost the wavefront as many round trips as its
 // unluckiest lane needed.  With the lane state kept as numbers and the
-// window's atomics left to lanes that hold an edge (together 2960 -> 2750
-// vector, 1820 -> 1510 scalar instructions a match): 64 mixed pairs, 473
-// thousand matches, K = 100: 2.07 -> 1.84 ms; 2048 x 1080 with 40000: 199 ->
-// 174 us; 1024 x 436 with 8000: 55.7 -> 48.7 us (kernel trace).
+// window's atomics left to lanes that hold an edge (together 3037 -> 2804
+// vector, 1879 -> 1547 scalar instructions a match on 64 mixed pairs of 444
+// thousand matches): 64 mixed pairs, 473 thousand matches, K = 100: 2.07 ->
+// 1.84 ms; 2048 x 1080 with 40000: 199 -> 174 us; 1024 x 436 with 8000: 55.7 ->
+// 48.7 us (kernel trace).
 template <int VCAP>
 struct NodeSlot {
     using T = typename std::conditional<(VCAP <= 256), u32, u64>::type;

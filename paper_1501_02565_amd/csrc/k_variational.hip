@@ -230,7 +230,8 @@ __global__ __launch_bounds__(256) void k_var_weights(VarArgs A, const float2* __
 // most of the rest is the launch itself, so a launch runs 16 (S = 20 saves a
 // quarter of the launches and gives it back in halo: 364 against 359 us a call
 // with 64 x 28 tiles).  With records in nine planes, all four neighbours from
-// LDS, S = 12 and 64 x 32 tiles a call took 626 us; now 359.
+// LDS, S = 12 and 64 x 32 tiles a call took 626 us; then 359 (348 with the warp
+// and the coefficients in one kernel).
 template <int TX_, int S_, int KP_, int NR_>
 struct VarTile {
     static constexpr int TX = TX_, S = S_, KP = KP_, NR = NR_;
@@ -240,9 +241,9 @@ struct VarTile {
     static_assert(TY > 0 && NT <= 1024, "tile");
     static long long tiles(int H, int W) { return (long long)((W + TX - 1) / TX) * ((H + TY - 1) / TY); }
 };
-// 32 x 32 pixels, 1024 threads of 2 rows: two workgroups fit a CU.  32 x 16
-// pixels, 768 threads: less work per CU where there are CUs to spare.  64 x 28
-// pixels, 720 threads of 4 rows: one per CU, and a third less halo.
+// 32 x 16 pixels, 768 threads of 2 rows: less work per CU where there are CUs to
+// spare.  32 x 32 pixels, 1024 threads of 2 rows: two workgroups fit a CU.  64 x
+// 28 pixels, 720 threads of 4 rows: one per CU, and a third less halo.
 using VarFine = VarTile<32, 16, 2, 24>;
 using VarSmall = VarTile<32, 16, 2, 32>;
 using VarWide = VarTile<64, 16, 4, 15>;
