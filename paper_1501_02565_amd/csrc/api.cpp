@@ -28,6 +28,7 @@ constexpr int kAutoPassesHistory = 8;   // recent needs the automatic budget cov
 constexpr int kAutoPassesMin = 4;
 constexpr int kRing = 4;             // descriptor upload slots
 constexpr int kMaxK = 256;
+constexpr int kMaxN = 1 << 26;        // 16 slots of the edge hash a match, at most 2^30
 constexpr int kStages = 8;
 constexpr int kProfRing = 64;
 const char* const kStageNames[kStages] = {"clear", "seed", "geodesic", "graph_emit",
@@ -151,14 +152,14 @@ int epic_validate(const float* cost, int H, int W, const float* matches, int N, 
     // vector loads and stores: matches rows are read as float4, flow as float2
     if (((uintptr_t)cost & 3) || ((uintptr_t)matches & 15) || ((uintptr_t)flow & 7)) return EPIC_ERR_ARG;
     if (H < 1 || W < 1 || N < 1 || K < 1 || K > kMaxK) return EPIC_ERR_ARG;
-    if ((long long)H * W >= (1LL << 31) || N >= (1 << 30)) return EPIC_ERR_ARG;
+    if ((long long)H * W >= (1LL << 31) || N > kMaxN) return EPIC_ERR_ARG;
     if (!std::isfinite(a) || a < 0.0f) return EPIC_ERR_ARG;
     if (mode != EPIC_NW && mode != EPIC_LA) return EPIC_ERR_ARG;
     return EPIC_OK;
 }
 
 size_t epic_workspace_bytes(int H, int W, int N, int K, int mode, int precision) {
-    if (H < 1 || W < 1 || N < 1 || K < 1 || K > kMaxK || (mode != 0 && mode != 1) ||
+    if (H < 1 || W < 1 || N < 1 || N > kMaxN || K < 1 || K > kMaxK || (mode != 0 && mode != 1) ||
         (precision != 0 && precision != 1) || (long long)H * W >= (1LL << 31))
         return 0;
     // the smallest tiling gives the largest tile-state array and queue ring
